@@ -40,9 +40,11 @@ namespace net {
 constexpr int NWG = 256;           // threads per workgroup (4 waves)
 constexpr int CH = 16;             // hidden channels (one MFMA tile)
 constexpr int MAX_LAYERS = 8;
-constexpr int DW_GRID = 256;       // workgroups of a weight-gradient launch
+constexpr int DW_GRID = 512;       // most workgroups per layer of the weight-gradient launch
 constexpr int DW_ELEMS = 9 * CH * CH;  // packed gradient of one layer [tap][co][ci]
-constexpr int RED_GRID = 512;      // workgroups of the loss / check reductions
+constexpr int RED_GRID = 512;      // workgroups of the check reduction
+constexpr int CONV_GRID = 4096;    // most workgroups of a convolution (and loss partials)
+constexpr int SCAN_GRID = 1024;    // most workgroups of the feature scan (and its maxima)
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -58,24 +60,6 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Pixel of tap t (ky = t / 3, kx = t % 3, offset (kx-1, ky-1)) from the
-// pixel at (x, y), or -1 outside the grid (zero padding).
-__device__ __forceinline__ int64_t tap_pixel_xy(int x, int y, int t, int nx, int ny)
-{
-    x += (t % 3) - 1;
-    y += (t / 3) - 1;
-    if (x < 0 || x >= nx || y < 0 || y >= ny)
-        return -1;
-    return (int64_t)y * nx + x;
-}
-
-__device__ __forceinline__ int64_t tap_pixel(int64_t p, int t, int nx, int ny, int64_t n)
-{
-    if (p >= n)
-        return -1;
-    return tap_pixel_xy((int)(p % nx), (int)(p / nx), t, nx, ny);
-}
-
 __device__ __forceinline__ bf16x4 load4(const uint16_t *a, int64_t idx)
 {
     return *reinterpret_cast<const bf16x4 *>(a + idx);  // idx is a multiple of 4
@@ -83,11 +67,27 @@ __device__ __forceinline__ bf16x4 load4(const uint16_t *a, int64_t idx)
 
 // ------------------------------------------------------------- convolution
 
+// One workgroup's sum of a double, valid in every thread.
+__device__ __forceinline__ double wg_sum(double v, double *lds)
+{
+    lds[threadIdx.x] = v;
+    __syncthreads();
+    for (int s = NWG / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s)
+            lds[threadIdx.x] += lds[threadIdx.x + s];
+        __syncthreads();
+    }
+    const double r = lds[0];
+    __syncthreads();
+    return r;
+}
+
 enum Epi : int {
-    EPI_ACT = 0,    // out = bf16(act(acc)), 16 channels (act: ReLU or identity)
-    EPI_MASK = 1,   // out = bf16(acc * act'(mask)), 16 channels (backward data)
-    EPI_Y = 2,      // y = acc of channel 0 (FP32 plane)
-    EPI_GUESS = 3,  // x0 = (ca xa + cb xb) + acc of channel 0 (FP64)
+    EPI_ACT = 0,   // out = bf16(act(acc)), 16 channels (act: ReLU or identity)
+    EPI_MASK = 1,  // out = bf16(acc * act'(mask)), 16 channels (backward data)
+    EPI_Y = 2,     // y = acc of channel 0 (FP32 plane)
+    EPI_LOSS = 3,  // d = acc of channel 0 - target: out = bf16(2 d / n) in channel 0
+                   // of 4, the workgroup's sum of d^2 to its loss partial
 };
 
 struct ConvArgs {
@@ -95,79 +95,114 @@ struct ConvArgs {
     int64_t n;
     const uint16_t *in;    // [n][CINP]
     const bf16x4 *w;       // packed operands [J][64]
-    uint16_t *out;         // EPI_RELU, EPI_MASK: [n][16]
+    uint16_t *out;         // EPI_ACT, EPI_MASK: [n][16]; EPI_LOSS: [n][4]
     const uint16_t *mask;  // EPI_MASK: [n][16]
     float *y;              // EPI_Y
-    double *x0;            // EPI_GUESS
-    const double *xa, *xb;  // EPI_GUESS: base guess ca xa + cb xb
-    double ca, cb;
-    int relu;               // EPI_ACT, EPI_MASK: 1 = ReLU, 0 = identity
+    const float *target;   // EPI_LOSS
+    double *loss;          // EPI_LOSS: one partial per workgroup
+    int relu;              // EPI_ACT, EPI_MASK: 1 = ReLU, 0 = identity
 };
 
+// Output tile of a convolution workgroup.
+constexpr int CTX = 32, CTY = 8;
+
+// A workgroup stages the input of a CTX x CTY tile plus one point on each
+// side in LDS (zeros outside the grid: the padding), and its waves run the
+// nine taps of 16-pixel chunks from there.  Reading the taps from global
+// memory instead, nine 8-byte loads per lane and chunk through the L1, bound the
+// kernel before (512 x 512, 16 -> 16 channels, 16.8 MB: 13.4 us; staged 9.6 us).
 template <int CINP, int EPI>
 __global__ __launch_bounds__(NWG) void k_conv(ConvArgs a)
 {
     constexpr int J = (9 * CINP + 15) / 16;
+    constexpr int RW = CTX + 2, RH = CTY + 2;
+    constexpr int PER = CINP == 16 ? 2 : 1;  // loads per pixel: 16 or 8 bytes
+    __shared__ __align__(16) uint16_t tile[RW * RH * CINP];
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4;
     const int px = lane & 15;
+    const int wv = threadIdx.x >> 6;
     bf16x4 w[J];
 #pragma unroll
     for (int j = 0; j < J; ++j)
         w[j] = a.w[j * 64 + lane];
-    const int64_t ntiles = (a.n + 15) / 16;
-    const int64_t wave = (int64_t)blockIdx.x * (NWG / 64) + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * (NWG / 64);
-    for (int64_t t = wave; t < ntiles; t += nwaves) {
-        const int64_t p = t * 16 + px;
-        const int x = (int)(p % a.nx), y = (int)(p / a.nx);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            int tap, c0;
+    const int tx = (a.nx + CTX - 1) / CTX;
+    const int64_t ntiles = (int64_t)tx * ((a.ny + CTY - 1) / CTY);
+    [[maybe_unused]] const float inv = 2.0f / (float)a.n;
+    [[maybe_unused]] double sum = 0.0;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int gx0 = (int)(t % tx) * CTX, gy0 = (int)(t / tx) * CTY;
+        if (t != (int64_t)blockIdx.x)
+            __syncthreads();  // the previous tile has been read
+        for (int e = threadIdx.x; e < RW * RH * PER; e += NWG) {
+            const int q = e / PER;
+            const int x = gx0 - 1 + q % RW, y = gy0 - 1 + q / RW;
+            const bool in = x >= 0 && x < a.nx && y >= 0 && y < a.ny;
+            const int64_t p = in ? (int64_t)y * a.nx + x : 0;
             if constexpr (CINP == 16) {
-                tap = j;
-                c0 = 4 * grp;
+                const uint4 v = in ? *reinterpret_cast<const uint4 *>(a.in + p * 16 + 8 * (e % PER)) : uint4{0, 0, 0, 0};
+                *reinterpret_cast<uint4 *>(&tile[e * 8]) = v;
             } else {
-                tap = 4 * j + grp;
-                c0 = 0;
+                const bf16x4 z = {0, 0, 0, 0};
+                *reinterpret_cast<bf16x4 *>(&tile[e * 4]) = in ? load4(a.in, p * 4) : z;
             }
-            bf16x4 b = {0, 0, 0, 0};
-            if (tap < 9 && p < a.n) {
-                const int64_t q = tap_pixel_xy(x, y, tap, a.nx, a.ny);
-                if (q >= 0)
-                    b = load4(a.in, q * CINP + c0);
-            }
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[j], b, acc, 0, 0, 0);
         }
-        if (p >= a.n)
-            continue;
-        // lane holds channels 4*grp .. 4*grp+3 of pixel p
-        if constexpr (EPI == EPI_ACT || EPI == EPI_MASK) {
-            bf16x4 o;
-            if constexpr (EPI == EPI_MASK) {
-                bf16x4 m = {1, 1, 1, 1};
-                if (a.relu)
-                    m = load4(a.mask, p * 16 + 4 * grp);
+        __syncthreads();
+        for (int c = wv; c < CTX / 16 * CTY; c += NWG / 64) {
+            const int qy = c / (CTX / 16), qx = c % (CTX / 16) * 16 + px;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    o[i] = (short)((!a.relu || bf2f((uint16_t)m[i]) > 0.f) ? f2bf(acc[i]) : 0);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    o[i] = (short)f2bf((!a.relu || acc[i] > 0.f) ? acc[i] : 0.f);
+            for (int j = 0; j < J; ++j) {
+                bf16x4 b = {0, 0, 0, 0};
+                if constexpr (CINP == 16) {
+                    b = *reinterpret_cast<const bf16x4 *>(&tile[((qy + j / 3) * RW + qx + j % 3) * 16 + 4 * grp]);
+                } else {
+                    const int tap = 4 * j + grp;
+                    if (tap < 9)
+                        b = *reinterpret_cast<const bf16x4 *>(&tile[((qy + tap / 3) * RW + qx + tap % 3) * 4]);
+                }
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[j], b, acc, 0, 0, 0);
             }
-            *reinterpret_cast<bf16x4 *>(a.out + p * 16 + 4 * grp) = o;
-        } else if constexpr (EPI == EPI_Y) {
-            if (grp == 0)
-                a.y[p] = acc[0];
-        } else {
-            if (grp == 0)
-                a.x0[p] = (a.ca * a.xa[p] + a.cb * a.xb[p]) + (double)acc[0];
+            const int x = gx0 + qx, y = gy0 + qy;
+            if (x >= a.nx || y >= a.ny)
+                continue;
+            const int64_t p = (int64_t)y * a.nx + x;
+            // lane holds channels 4*grp .. 4*grp+3 of pixel p
+            if constexpr (EPI == EPI_ACT || EPI == EPI_MASK) {
+                bf16x4 o;
+                if constexpr (EPI == EPI_MASK) {
+                    bf16x4 m = {1, 1, 1, 1};
+                    if (a.relu)
+                        m = load4(a.mask, p * 16 + 4 * grp);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        o[i] = (short)((!a.relu || bf2f((uint16_t)m[i]) > 0.f) ? f2bf(acc[i]) : 0);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        o[i] = (short)f2bf((!a.relu || acc[i] > 0.f) ? acc[i] : 0.f);
+                }
+                *reinterpret_cast<bf16x4 *>(a.out + p * 16 + 4 * grp) = o;
+            } else if (grp == 0) {
+                if constexpr (EPI == EPI_Y) {
+                    a.y[p] = acc[0];
+                } else {
+                    const float d = acc[0] - a.target[p];
+                    sum += (double)d * (double)d;
+                    bf16x4 o = {0, 0, 0, 0};
+                    o[0] = (short)f2bf(d * inv);
+                    *reinterpret_cast<bf16x4 *>(a.out + p * 4) = o;
+                }
+            }
         }
     }
+    if constexpr (EPI == EPI_LOSS) {
+        __shared__ double red[NWG];
+        const double s = wg_sum(sum, red);
+        if (threadIdx.x == 0)
+            a.loss[blockIdx.x] = s;
+    }
 }
-
 
 // ------------------------------------------------------ residual rows
 
@@ -374,14 +409,63 @@ __global__ __launch_bounds__(FWAVES * 64) void k_net_fused(FusedArgs a)
 
 // ------------------------------------------------------- weight gradient
 
-// Partial dW[tap][co][ci] = sum over pixels p of G[p][co] * X[p + tap][ci]
-// for this workgroup's tiles: one MFMA per tap and 16-pixel tile (K =
-// pixels).  The four waves are summed in wave order in LDS.
-template <int CINP, int GP>
-__global__ __launch_bounds__(NWG) void k_dw(int nx, int ny, int64_t n, const uint16_t *act,
-                                              const uint16_t *g, float *partials)
+// dW[tap][co][ci] = sum over pixels p of G[p][co] * X[p + tap][ci]: a GEMM
+// whose K index is the pixel, one MFMA per tap and 16 pixels.  A lane's
+// operand is four consecutive pixels of one channel, which in the
+// pixel-major planes lie 2 bytes apart every 32: a workgroup therefore
+// stages the tile of G and the tile plus a border of X in LDS
+// channel-major, where the operand is one 8-byte read, and the taps one
+// point to the left and right are the same words shifted by 16 bits.
+// (Gathering the operands from global memory, 40 two-byte loads per lane
+// and chunk with their pixel arithmetic, took 158-165 us per layer at
+// 512 x 512; all four layers take one launch of 28 us now.)
+// Channel pitches are 8 words modulo the 64 banks, so the 16 channels x 4
+// pixel groups of a wave's read cover every bank twice.
+constexpr int DTX = 32, DTY = 16;               // tile
+constexpr int DXP = DTX + 4;                    // X row: pixel x at x - gx0 + 2
+constexpr int DXC = DXP * (DTY + 2) + 8;        // X channel pitch (328 words)
+constexpr int DGC = DTX * DTY + 16;             // G channel pitch (264 words)
+static_assert(DXC / 2 % 64 == 8 && DGC / 2 % 64 == 8, "bank spread of the channel pitches");
+
+struct DwArgs {
+    int nx, ny, layers;
+    const uint16_t *act[MAX_LAYERS];  // input of layer l: [n][4] (l = 0) or [n][16]
+    const uint16_t *g[MAX_LAYERS];    // gradient of its output: [n][4] (last) or [n][16]
+    float *partials;                  // [layer][gridDim.x][DW_ELEMS]
+};
+
+// Stage channels 0 .. C-1 (four at a time, two pixels to a word) of `rows`
+// rows from (x0, y0): pixel pairs x0 + 2 i, i < pairs, at word
+// c * pitch / 2 + row * pairs + i.  Zeros outside the grid.
+template <int C>
+__device__ __forceinline__ void stage_planes(const uint16_t *src, int nx, int ny, int x0, int y0, int pairs,
+                                             int rows, int pitch, uint32_t *dst)
 {
-    __shared__ float red[DW_ELEMS];
+    constexpr int Q = C / 4;
+    for (int e = threadIdx.x; e < pairs * rows * Q; e += NWG) {
+        const int q = e % Q, i = e / Q % pairs, r = e / Q / pairs;
+        const int x = x0 + 2 * i, y = y0 + r;
+        const bool row = y >= 0 && y < ny;
+        bf16x4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+        if (row && x >= 0 && x < nx)
+            a = load4(src, ((int64_t)y * nx + x) * C + 4 * q);
+        if (row && x + 1 >= 0 && x + 1 < nx)
+            b = load4(src, ((int64_t)y * nx + x + 1) * C + 4 * q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            dst[(4 * q + k) * (pitch / 2) + r * pairs + i] = (uint32_t)(uint16_t)a[k] | (uint32_t)(uint16_t)b[k] << 16;
+    }
+}
+
+__device__ __forceinline__ bf16x4 quad(uint32_t lo, uint32_t hi)
+{
+    return __builtin_bit_cast(bf16x4, uint2{lo, hi});
+}
+
+template <int CINP, int GP>
+__device__ __forceinline__ void dw_layer(const DwArgs &d, int l, uint32_t *lds)
+{
+    uint32_t *xs = lds, *gs = lds + CH * DXC / 2;
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4;
     const int col = lane & 15;  // row co of A, column ci of B
@@ -390,30 +474,41 @@ __global__ __launch_bounds__(NWG) void k_dw(int nx, int ny, int64_t n, const uin
 #pragma unroll
     for (int t = 0; t < 9; ++t)
         acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int64_t ntiles = (n + 15) / 16;
-    const int64_t wave = (int64_t)blockIdx.x * (NWG / 64) + wv;
-    const int64_t nwaves = (int64_t)gridDim.x * (NWG / 64);
-    for (int64_t t = wave; t < ntiles; t += nwaves) {
-        const int64_t p0 = t * 16 + 4 * grp;
-        bf16x4 av = {0, 0, 0, 0};
+    const int tx = (d.nx + DTX - 1) / DTX;
+    const int64_t ntiles = (int64_t)tx * ((d.ny + DTY - 1) / DTY);
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int gx0 = (int)(t % tx) * DTX, gy0 = (int)(t / tx) * DTY;
+        if (t != (int64_t)blockIdx.x)
+            __syncthreads();  // the previous tile has been read
+        stage_planes<CINP>(d.act[l], d.nx, d.ny, gx0 - 2, gy0 - 1, DXP / 2, DTY + 2, DXC, xs);
+        stage_planes<GP>(d.g[l], d.nx, d.ny, gx0, gy0, DTX / 2, DTY, DGC, gs);
+        __syncthreads();
+        for (int c = wv; c < DTX / 16 * DTY; c += NWG / 64) {
+            const int y = c / (DTX / 16), w0 = c % (DTX / 16) * 8 + 2 * grp;  // first word of the lane's pixels
+            bf16x4 av = {0, 0, 0, 0};
+            if (col < GP)
+                av = __builtin_bit_cast(bf16x4, *reinterpret_cast<const uint2 *>(&gs[col * (DGC / 2) + y * (DTX / 2) + w0]));
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (col < GP && p0 + q < n)
-                av[q] = (short)g[(p0 + q) * GP + col];
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            bf16x4 bv = {0, 0, 0, 0};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t s = tap_pixel(p0 + q, tap, nx, ny, n);
-                if (col < CINP && s >= 0)
-                    bv[q] = (short)act[s * CINP + col];
+            for (int ky = 0; ky < 3; ++ky) {
+                uint2 p = {0, 0}, q = {0, 0};  // pixels -2 .. 1 and 2 .. 5 from the lane's first
+                if (col < CINP) {
+                    const uint32_t *row = &xs[col * (DXC / 2) + (y + ky) * (DXP / 2) + w0];
+                    p = *reinterpret_cast<const uint2 *>(row);
+                    q = *reinterpret_cast<const uint2 *>(row + 2);
+                }
+                const uint32_t left = __builtin_amdgcn_alignbit(p.y, p.x, 16);
+                const uint32_t mid = __builtin_amdgcn_alignbit(q.x, p.y, 16);
+                const uint32_t right = __builtin_amdgcn_alignbit(q.y, q.x, 16);
+                acc[3 * ky] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, quad(left, mid), acc[3 * ky], 0, 0, 0);
+                acc[3 * ky + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, quad(p.y, q.x), acc[3 * ky + 1], 0, 0, 0);
+                acc[3 * ky + 2] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, quad(mid, right), acc[3 * ky + 2], 0, 0, 0);
             }
-            acc[tap] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[tap], 0, 0, 0);
         }
     }
-    // acc[tap][i] = D[co = 4*grp + i][ci = col]
+    // acc[tap][i] = D[co = 4*grp + i][ci = col]; the waves in wave order
+    float *red = reinterpret_cast<float *>(lds);
     for (int w = 0; w < NWG / 64; ++w) {
+        __syncthreads();
         if (wv == w) {
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap)
@@ -423,10 +518,25 @@ __global__ __launch_bounds__(NWG) void k_dw(int nx, int ny, int64_t n, const uin
                     red[e] = (w == 0) ? acc[tap][i] : red[e] + acc[tap][i];
                 }
         }
-        __syncthreads();
     }
+    __syncthreads();
+    float *out = d.partials + ((size_t)l * gridDim.x + blockIdx.x) * DW_ELEMS;
     for (int e = threadIdx.x; e < DW_ELEMS; e += NWG)
-        partials[(size_t)blockIdx.x * DW_ELEMS + e] = red[e];
+        out[e] = red[e];
+}
+
+// All layers in one launch: blockIdx.y is the layer.
+__global__ __launch_bounds__(NWG) void k_dw(DwArgs d)
+{
+    __shared__ __align__(16) uint32_t lds[CH * (DXC + DGC) / 2];
+    static_assert(CH * (DXC + DGC) / 2 >= DW_ELEMS, "the wave sums reuse the staged tiles");
+    const int l = blockIdx.y;
+    if (l == 0)
+        dw_layer<4, 16>(d, l, lds);
+    else if (l == d.layers - 1)
+        dw_layer<16, 4>(d, l, lds);
+    else
+        dw_layer<16, 16>(d, l, lds);
 }
 
 struct LayerMeta {
@@ -442,19 +552,47 @@ struct NetMeta {
     LayerMeta l[MAX_LAYERS];
 };
 
-// Second stage: grad[canonical] = sum over workgroups, in workgroup order.
-__global__ __launch_bounds__(NWG) void k_dw_reduce(const float *partials, int nparts, LayerMeta m,
-                                                   float *grad)
+// Second stage of the weight gradient: grad[canonical] = sum over the
+// workgroups' partials, blockIdx.y the layer.  A workgroup takes 64 elements;
+// its wave w sums the w-th quarter of the partials in order, sixteen loads
+// in flight (one thread per element adding 256 partials one after the other
+// took 59 us per layer at 512 x 512; now 6 us for four layers), and the quarters are added in order.  The row of
+// workgroups after the last layer sums the loss partials.
+constexpr int DWR = DW_ELEMS / 64;  // workgroups per layer
+
+__global__ __launch_bounds__(NWG) void k_grad_reduce(const float *partials, int nparts, NetMeta nm, float *grad,
+                                                     const double *losspart, int nloss, int64_t n, double *loss)
 {
-    for (int e = blockIdx.x * NWG + threadIdx.x; e < DW_ELEMS; e += gridDim.x * NWG) {
-        const int tap = e / 256, co = (e / 16) % 16, ci = e % 16;
-        if (co >= m.cout || ci >= m.cin)
-            continue;
-        float s = 0.f;
-        for (int w = 0; w < nparts; ++w)
-            s += partials[(size_t)w * DW_ELEMS + e];
-        grad[m.woff + (co * m.cin + ci) * 9 + tap] = s;
+    if ((int)blockIdx.y == nm.layers) {
+        __shared__ double lds[NWG];
+        if (blockIdx.x != 0)
+            return;
+        double v = 0.0;
+        for (int w = threadIdx.x; w < nloss; w += NWG)
+            v += losspart[w];
+        const double s = wg_sum(v, lds);
+        if (threadIdx.x == 0)
+            *loss = s / (double)n;
+        return;
     }
+    __shared__ float red[NWG];
+    const LayerMeta m = nm.l[blockIdx.y];
+    const int e = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int wv = threadIdx.x >> 6;
+    const float *src = partials + (size_t)blockIdx.y * nparts * DW_ELEMS + e;
+    const int w0 = nparts * wv / 4, w1 = nparts * (wv + 1) / 4;
+    float s = 0.f;
+#pragma unroll 16
+    for (int w = w0; w < w1; ++w)
+        s += src[(size_t)w * DW_ELEMS];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (wv != 0)
+        return;
+    s = ((red[threadIdx.x] + red[threadIdx.x + 64]) + red[threadIdx.x + 128]) + red[threadIdx.x + 192];
+    const int tap = e / 256, co = (e / 16) % 16, ci = e % 16;
+    if (co < m.cout && ci < m.cin)
+        grad[m.woff + (co * m.cin + ci) * 9 + tap] = s;
 }
 
 // ------------------------------------------------- weights: Adam and packing
@@ -513,21 +651,47 @@ __global__ __launch_bounds__(NWG) void k_pack(NetMeta nm, const float *wcan, bf1
 
 enum FeatMode : int {
     FEAT_RAW = 0,   // inference: the plane r as it is
-    FEAT_SCAN = 1,  // training, pass 1: r to rbuf, max |r| to *maxbits
+    FEAT_SCAN = 1,  // training, pass 1: r to rbuf, each workgroup's max |r| to maxbits
     FEAT_NORM = 2,  // training, pass 2: plane and target divided by max |r|
 };
 
+// The workgroup's maximum, valid in every thread.
+__device__ __forceinline__ unsigned long long wg_max(unsigned long long v, unsigned long long *lds)
+{
+    lds[threadIdx.x] = v;
+    __syncthreads();
+    for (int s = NWG / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s)
+            lds[threadIdx.x] = max(lds[threadIdx.x], lds[threadIdx.x + s]);
+        __syncthreads();
+    }
+    return lds[0];
+}
+
 // One thread per row.  The base guess x = ca xa + cb xb is formed at every
 // column the row touches; r = b - A x with the row summed left to right.
-// Input plane [n][4] = (r, 0, 0, 0).
+// Input plane [n][4] = (r, 0, 0, 0).  The maximum of |r| is taken over the
+// bits of the doubles (order-independent), per workgroup in the scan and
+// over the nmax workgroups in the second pass: one atomic per row on a
+// single word held the scan at 56 us for 262,144 rows (now 11 us).
 template <int MODE>
 __global__ __launch_bounds__(NWG) void k_features(DevCsr A, const double *b, const double *xa,
                                                   const double *xb, double ca, double cb,
                                                   const double *unext, double *rbuf,
-                                                  unsigned long long *maxbits, uint16_t *feat,
+                                                  unsigned long long *maxbits, int nmax, uint16_t *feat,
                                                   float *target)
 {
+    [[maybe_unused]] __shared__ unsigned long long lds[NWG];
     const int64_t n = A.n;
+    [[maybe_unused]] unsigned long long top = 0;
+    double s = 1.0;
+    if constexpr (MODE == FEAT_NORM) {
+        for (int w = threadIdx.x; w < nmax; w += NWG)
+            top = max(top, maxbits[w]);
+        s = __longlong_as_double((long long)wg_max(top, lds));
+        if (!(s > 0.0))
+            s = 1.0;
+    }
     for (int64_t i = (int64_t)blockIdx.x * NWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * NWG) {
         double r;
         if constexpr (MODE == FEAT_NORM) {
@@ -537,70 +701,23 @@ __global__ __launch_bounds__(NWG) void k_features(DevCsr A, const double *b, con
         }
         if constexpr (MODE == FEAT_SCAN) {
             rbuf[i] = r;
-            atomicMax(maxbits, (unsigned long long)__double_as_longlong(fabs(r)));
+            top = max(top, (unsigned long long)__double_as_longlong(fabs(r)));
             continue;
         }
-        double s = 1.0;
-        if constexpr (MODE == FEAT_NORM) {
-            s = __longlong_as_double((long long)*maxbits);
-            if (!(s > 0.0))
-                s = 1.0;
+        if constexpr (MODE == FEAT_NORM)
             target[i] = (float)((unext[i] - (ca * xa[i] + cb * xb[i])) / s);
-        }
         bf16x4 o = {0, 0, 0, 0};
         o[0] = (short)f2bf((float)(r / s));
         *reinterpret_cast<bf16x4 *>(feat + i * 4) = o;
     }
-}
-
-__global__ void k_zero_u64(unsigned long long *p) { *p = 0ull; }
-
-// ---------------------------------------------------------- loss, check
-
-__device__ __forceinline__ double wg_sum(double v, double *lds)
-{
-    lds[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = NWG / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            lds[threadIdx.x] += lds[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = lds[0];
-    __syncthreads();
-    return r;
-}
-
-// Mean squared error of y against target; dy = 2 (y - t) / n into channel 0
-// of the output gradient plane ([n][4] BF16).
-__global__ __launch_bounds__(NWG) void k_loss(int64_t n, const float *y, const float *t, uint16_t *gout,
-                                              double *partials)
-{
-    __shared__ double lds[NWG];
-    double acc = 0.0;
-    const float inv = 2.0f / (float)n;
-    for (int64_t i = (int64_t)blockIdx.x * NWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * NWG) {
-        const float d = y[i] - t[i];
-        acc += (double)d * (double)d;
-        bf16x4 o = {0, 0, 0, 0};
-        o[0] = (short)f2bf(d * inv);
-        *reinterpret_cast<bf16x4 *>(gout + i * 4) = o;
-    }
-    const double s = wg_sum(acc, lds);
-    if (threadIdx.x == 0)
-        partials[blockIdx.x] = s;
-}
-
-__global__ __launch_bounds__(NWG) void k_loss_final(int nparts, const double *partials, int64_t n,
-                                                    double *loss)
-{
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < nparts; ++w)
-            s += partials[w];
-        *loss = s / (double)n;
+    if constexpr (MODE == FEAT_SCAN) {
+        top = wg_max(top, lds);
+        if (threadIdx.x == 0)
+            maxbits[blockIdx.x] = top;
     }
 }
+
+// ---------------------------------------------------------------- check
 
 // ||b - A x0||^2 and ||b - A u_m||^2, per workgroup.
 __global__ __launch_bounds__(NWG) void k_check(DevCsr A, const double *b, const double *x0,
@@ -669,13 +786,13 @@ struct fk_net_s {
     int64_t cap = 0;
     uint16_t *feat = nullptr;             // [n][4]
     uint16_t *act[MAX_LAYERS] = {};       // act[l], l = 1..L-1: [n][16]
-    uint16_t *g16[2] = {nullptr, nullptr};  // [n][16] gradient ping-pong
+    uint16_t *g16[MAX_LAYERS] = {};       // g16[l], l = 0..L-2: [n][16] gradient of layer l's output
     uint16_t *g4 = nullptr;               // [n][4] output gradient
     float *y = nullptr, *target = nullptr;
     double *rbuf = nullptr;
-    unsigned long long *maxbits = nullptr;
-    float *dwpart = nullptr;
-    double *redpart = nullptr, *loss = nullptr;
+    unsigned long long *maxbits = nullptr;  // [SCAN_GRID]
+    float *dwpart = nullptr;              // [L][DW_GRID][DW_ELEMS]
+    double *redpart = nullptr, *losspart = nullptr, *loss = nullptr;
     int32_t *flag = nullptr;
     double *xtmp = nullptr;               // [n] ping-pong iterate of multi-pass guesses
 };
@@ -731,8 +848,8 @@ void release_workspace(fk_net N)
     dfree(N->feat);
     for (auto &a : N->act)
         dfree(a);
-    dfree(N->g16[0]);
-    dfree(N->g16[1]);
+    for (auto &g : N->g16)
+        dfree(g);
     dfree(N->g4);
     dfree(N->y);
     dfree(N->target);
@@ -740,6 +857,7 @@ void release_workspace(fk_net N)
     dfree(N->maxbits);
     dfree(N->dwpart);
     dfree(N->redpart);
+    dfree(N->losspart);
     dfree(N->loss);
     dfree(N->flag);
     dfree(N->xtmp);
@@ -762,15 +880,16 @@ fk_status ensure_workspace(fk_net N, int64_t n)
     e = e ? e : dalloc(&N->feat, un * 4);
     for (int l = 1; l < N->meta.layers && e == hipSuccess; ++l)
         e = dalloc(&N->act[l], un * 16);
-    e = e ? e : dalloc(&N->g16[0], un * 16);
-    e = e ? e : dalloc(&N->g16[1], un * 16);
+    for (int l = 0; l < N->meta.layers - 1 && e == hipSuccess; ++l)
+        e = dalloc(&N->g16[l], un * 16);
     e = e ? e : dalloc(&N->g4, un * 4);
     e = e ? e : dalloc(&N->y, un);
     e = e ? e : dalloc(&N->target, un);
     e = e ? e : dalloc(&N->rbuf, un);
-    e = e ? e : dalloc(&N->maxbits, 1);
-    e = e ? e : dalloc(&N->dwpart, (size_t)DW_GRID * DW_ELEMS);
+    e = e ? e : dalloc(&N->maxbits, (size_t)SCAN_GRID);
+    e = e ? e : dalloc(&N->dwpart, (size_t)N->meta.layers * DW_GRID * DW_ELEMS);
     e = e ? e : dalloc(&N->redpart, (size_t)2 * RED_GRID);
+    e = e ? e : dalloc(&N->losspart, (size_t)CONV_GRID);
     e = e ? e : dalloc(&N->loss, 1);
     e = e ? e : dalloc(&N->flag, 1);
     e = e ? e : dalloc(&N->xtmp, un);
@@ -800,17 +919,20 @@ fk_status check_grid(fk_net N, fk_csr A, int32_t nx, int32_t ny, DevCsr *view)
     return ensure_workspace(N, view->n);
 }
 
-// Forward through all layers from N->feat; the last layer writes y
-// (x0 == nullptr) or x0 = (ca xa + cb xb) + y.
-hipError_t forward(fk_net N, int nx, int ny, int64_t n, double *x0, const double *xa, const double *xb,
-                   double ca, double cb, hipStream_t s)
+int64_t tiles_of(int nx, int ny, int tx, int ty)
+{
+    return (int64_t)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+}
+
+// Forward through all layers from N->feat; the last layer writes y, or
+// (with a target) the output gradient N->g4 and the loss partials.
+hipError_t forward(fk_net N, int nx, int ny, int64_t n, const float *target, hipStream_t s)
 {
     const int L = N->meta.layers;
-    const int grid = grid_for((n + 15) / 16, NWG / 64, 4096);
+    const int grid = grid_for(tiles_of(nx, ny, CTX, CTY), 1, CONV_GRID);
     const uint16_t *in = N->feat;
     for (int l = 0; l < L; ++l) {
-        const LayerMeta &m = N->meta.l[l];
-        ConvArgs a{nx, ny, n, in, N->packed + m.pf, nullptr, nullptr, nullptr, nullptr, xa, xb, ca, cb,
+        ConvArgs a{nx, ny, n, in, N->packed + N->meta.l[l].pf, nullptr, nullptr, nullptr, nullptr, nullptr,
                    N->meta.relu};
         if (l < L - 1) {
             a.out = N->act[l + 1];
@@ -819,9 +941,11 @@ hipError_t forward(fk_net N, int nx, int ny, int64_t n, double *x0, const double
             else
                 hipLaunchKernelGGL((k_conv<16, EPI_ACT>), dim3(grid), dim3(NWG), 0, s, a);
             in = N->act[l + 1];
-        } else if (x0) {
-            a.x0 = x0;
-            hipLaunchKernelGGL((k_conv<16, EPI_GUESS>), dim3(grid), dim3(NWG), 0, s, a);
+        } else if (target) {
+            a.out = N->g4;
+            a.target = target;
+            a.loss = N->losspart;
+            hipLaunchKernelGGL((k_conv<16, EPI_LOSS>), dim3(grid), dim3(NWG), 0, s, a);
         } else {
             a.y = N->y;
             hipLaunchKernelGGL((k_conv<16, EPI_Y>), dim3(grid), dim3(NWG), 0, s, a);
@@ -831,48 +955,44 @@ hipError_t forward(fk_net N, int nx, int ny, int64_t n, double *x0, const double
 }
 
 // Normalised features and target of one training sample, forward, loss and
-// backward: the gradient lands in N->grad, the loss in N->loss.
+// backward: the gradient lands in N->grad, the loss in N->loss.  The
+// backward data pass keeps every layer's gradient plane, so that the weight
+// gradients of all layers are one launch after it.
 hipError_t loss_and_gradient(fk_net N, const DevCsr &A, int nx, int ny, const double *b, const double *um,
                              const double *um1, const double *unext, hipStream_t s)
 {
     const int64_t n = A.n;
     const int L = N->meta.layers;
-    const int gv = grid_for(n, NWG, 2048);
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, N->maxbits);
-    hipLaunchKernelGGL((k_features<FEAT_SCAN>), dim3(gv), dim3(NWG), 0, s, A, b, um, um1, 2.0, -1.0, unext,
-                       N->rbuf, N->maxbits, N->feat, N->target);
-    hipLaunchKernelGGL((k_features<FEAT_NORM>), dim3(gv), dim3(NWG), 0, s, A, b, um, um1, 2.0, -1.0, unext,
-                       N->rbuf, N->maxbits, N->feat, N->target);
-    hipError_t e = forward(N, nx, ny, n, nullptr, um, um1, 2.0, -1.0, s);
+    const int gf = grid_for(n, NWG, SCAN_GRID);
+    hipLaunchKernelGGL((k_features<FEAT_SCAN>), dim3(gf), dim3(NWG), 0, s, A, b, um, um1, 2.0, -1.0, unext,
+                       N->rbuf, N->maxbits, 0, N->feat, N->target);
+    hipLaunchKernelGGL((k_features<FEAT_NORM>), dim3(gf), dim3(NWG), 0, s, A, b, um, um1, 2.0, -1.0, unext,
+                       N->rbuf, N->maxbits, gf, N->feat, N->target);
+    hipError_t e = forward(N, nx, ny, n, N->target, s);
     if (e != hipSuccess)
         return e;
-    const int gl = grid_for(n, NWG, RED_GRID);
-    hipLaunchKernelGGL(k_loss, dim3(gl), dim3(NWG), 0, s, n, N->y, N->target, N->g4, N->redpart);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(NWG), 0, s, gl, N->redpart, n, N->loss);
-    const int gc = grid_for((n + 15) / 16, NWG / 64, 4096);
-    const uint16_t *gcur = N->g4;  // gradient w.r.t. the output of layer l
-    int pp = 0;
-    for (int l = L - 1; l >= 0; --l) {
-        const LayerMeta &m = N->meta.l[l];
-        const uint16_t *act = l == 0 ? N->feat : N->act[l];
-        if (l == 0)
-            hipLaunchKernelGGL((k_dw<4, 16>), dim3(DW_GRID), dim3(NWG), 0, s, nx, ny, n, act, gcur, N->dwpart);
-        else if (l == L - 1)
-            hipLaunchKernelGGL((k_dw<16, 4>), dim3(DW_GRID), dim3(NWG), 0, s, nx, ny, n, act, gcur, N->dwpart);
+    const int gc = grid_for(tiles_of(nx, ny, CTX, CTY), 1, CONV_GRID);
+    DwArgs d{};
+    d.nx = nx;
+    d.ny = ny;
+    d.layers = L;
+    d.partials = N->dwpart;
+    d.act[0] = N->feat;
+    d.g[L - 1] = N->g4;
+    for (int l = L - 1; l > 0; --l) {
+        d.act[l] = N->act[l];
+        d.g[l - 1] = N->g16[l - 1];
+        ConvArgs a{nx, ny, n, d.g[l], N->packed + N->meta.l[l].pt, N->g16[l - 1], N->act[l], nullptr, nullptr,
+                   nullptr, N->meta.relu};
+        if (l == L - 1)
+            hipLaunchKernelGGL((k_conv<4, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
         else
-            hipLaunchKernelGGL((k_dw<16, 16>), dim3(DW_GRID), dim3(NWG), 0, s, nx, ny, n, act, gcur, N->dwpart);
-        hipLaunchKernelGGL(k_dw_reduce, dim3(DW_ELEMS / NWG), dim3(NWG), 0, s, N->dwpart, DW_GRID, m, N->grad);
-        if (l > 0) {
-            ConvArgs a{nx, ny, n, gcur, N->packed + m.pt, N->g16[pp], N->act[l], nullptr, nullptr, nullptr, nullptr,
-                       0.0, 0.0, N->meta.relu};
-            if (l == L - 1)
-                hipLaunchKernelGGL((k_conv<4, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
-            else
-                hipLaunchKernelGGL((k_conv<16, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
-            gcur = N->g16[pp];
-            pp ^= 1;
-        }
+            hipLaunchKernelGGL((k_conv<16, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
     }
+    const int gd = grid_for(tiles_of(nx, ny, DTX, DTY), 1, DW_GRID);
+    hipLaunchKernelGGL(k_dw, dim3(gd, L), dim3(NWG), 0, s, d);
+    hipLaunchKernelGGL(k_grad_reduce, dim3(DWR, L + 1), dim3(NWG), 0, s, N->dwpart, gd, N->meta, N->grad,
+                       N->losspart, gc, n, N->loss);
     return hipGetLastError();
 }
 
@@ -987,8 +1107,8 @@ extern "C" fk_status fk_net_forward(fk_net N, fk_csr Ah, int32_t nx, int32_t ny,
     hipStream_t s = (hipStream_t)stream;
     const int64_t n = A.n;
     hipLaunchKernelGGL((k_features<FEAT_RAW>), dim3(grid_for(n, NWG, 2048)), dim3(NWG), 0, s, A, b, um, um1,
-                       2.0, -1.0, nullptr, nullptr, nullptr, N->feat, nullptr);
-    NET_HIP(forward(N, nx, ny, n, nullptr, um, um1, 2.0, -1.0, s));
+                       2.0, -1.0, nullptr, nullptr, nullptr, 0, N->feat, nullptr);
+    NET_HIP(forward(N, nx, ny, n, nullptr, s));
     NET_HIP(hipMemcpyAsync(y, N->y, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     NET_HIP(hipStreamSynchronize(s));
     return FK_OK;

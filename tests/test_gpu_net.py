@@ -199,6 +199,25 @@ def test_gradient_matches_oracle(nx, ny, act, device):
     assert np.dot(grad, grad_ref) > 0.99 * np.linalg.norm(grad) * np.linalg.norm(grad_ref)
 
 
+# Tile edges of the staged convolutions (32 x 8) and weight gradients
+# (32 x 16): one point more and less, a single column, more tiles than one
+# workgroup's share of a weight-gradient launch (512), the fewest and most layers.
+@pytest.mark.parametrize("nx,ny,layers", [(1, 40, 3), (31, 16, 2), (33, 17, 3), (65, 9, 2), (32, 15, 8),
+                                          (530, 500, 2)])
+def test_gradient_tile_edges(nx, ny, layers, device):
+    print(f"\n[case] net gradient {nx}x{ny}, {layers} layers", flush=True)
+    A = P.heat2d(nx, ny=ny)
+    M = fk.Matrix(A)
+    b, um, um1, un = _inputs(nx, ny, 9)
+    w = P.net_init(layers, 4)
+    grad, loss = fk.Net(layers, w).gradient(M, nx, ny, dev(b), dev(um), dev(um1), dev(un))
+    planes, _, target, _ = ON.features(A, nx, ny, b, um, um1, unext=un, normalize=True)
+    loss_ref, grad_ref = ON.loss_and_gradient(w, planes, target.reshape(ny, nx), layers)
+    # no worse than every rounding moved by one BF16 unit (2^-8 relative)
+    assert abs(loss - loss_ref) <= 2.0 ** -8 * loss_ref, (loss, loss_ref)
+    assert _rel(grad, grad_ref) <= 2.0 ** -8, _rel(grad, grad_ref)
+
+
 def test_training_reproducible_and_descends(device):
     """Two networks trained from the same weights on the same samples end
     bit-identical; the loss falls."""
