@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstddef>
@@ -872,7 +873,8 @@ struct fk_solver_s {
     DevState *st = nullptr;
     int32_t hist_cap = 0;
     // pinned: [0] state written before a (inner) solve, [1] before the
-    // refinement's first residual, [2] state read back
+    // refinement's first residual, [2] state read back ([3] a resident
+    // launch's ResCtl, which lies behind the device state)
     DevState *h_init = nullptr;
     int32_t *h_status = nullptr;    // pinned, two poll slots
     hipEvent_t poll_ev[2] = {nullptr, nullptr};
@@ -897,6 +899,14 @@ struct fk_solver_s {
     int graph_iters = 0;
     bool small = false;        // whole solve in one single-workgroup launch
     bool small_stage = false;  // ... with the matrix staged in LDS
+    // Whole solve in one launch of resident workgroups: shape, workspace
+    // (one allocation) and the next launch's first tag.
+    bool resident = false;
+    ResShape res{};
+    ResArgs res_args{};
+    char *res_mem = nullptr;
+    size_t res_words = 0;  // tagged words at its start, zero before the first tag
+    uint32_t res_epoch = 1;
     // FK_CG_MIXED: FP32 inner vectors and matrix values; the refinement's
     // own state (st is the inner solver's); sweeps of the last solve.
     bool mixed = false;
@@ -953,6 +963,7 @@ static void solver_release(fk_solver S)
     dev_free(S->gR);
     dev_free(S->geta);
     dev_free(S->gpart);
+    dev_free(S->res_mem);
     if (S->h_init)
         (void)hipHostFree(S->h_init);
     if (S->h_status)
@@ -1046,6 +1057,107 @@ static int fused_grid(fk_csr A, int step, int grid_spmv)
     if (g >= 8)
         g = (g + 7) & ~(int64_t)7;
     return (int)std::max<int64_t>(g, 1);
+}
+
+// Compute units that resident solves of this process hold, per device: two
+// solves at a time (on two streams or threads) take the resident path only
+// while their workgroups fit the chip together.
+static std::atomic<int> &resident_units(int device)
+{
+    static std::atomic<int> units[64];
+    return units[device & 63];
+}
+
+// Iterations of one resident launch; longer solves continue in the next.
+constexpr int RES_CHUNK = 8192;
+// Fewest unknowns of a resident solve: below, one workgroup solves alone
+// (2D Poisson, us per iteration, one workgroup / resident / launch per step:
+// 3.4 / 3.8 / 12 at n = 1,024; 9.9 / 3.6 / 12 at 3,969; - / 4.2 / 11.6 at
+// 16,129; - / 6.7 / 15.9 at 261,121; - / 11.8 / 29.4 at 1,000,000; 3D: - /
+// 7.5 / 17.4 at 262,144; - / 13.8 / 23.5 at 512,000).
+constexpr int64_t RES_MIN_N = 4096;
+
+// Which solves are resident: pipelined CG on a sliced layout of at most
+// seven entries per row whose rows, with their ghosts, fit the chip (the
+// streaming mode is for matrices far beyond it, or asked for).
+static bool resident_ok(fk_csr A, const fk_opts &o)
+{
+    if (o.flags & (FK_FLAG_GRAPH | FK_FLAG_PROFILE))  // these time or replay the launches
+        return false;
+    if (o.method != FK_CG_PIPELINED && o.method != FK_CG_PIPELINED_1K)
+        return false;
+    return A->sliced() && !A->streaming() && A->n >= RES_MIN_N;
+}
+
+// The resident workspace of a new solver; leaves S->resident false where the
+// matrix does not fit (or the workspace does not).
+static fk_status resident_create(fk_solver S)
+{
+    fk_csr A = S->A;
+    const DevCsr view = A->view();
+    const size_t max_lds = max_lds_per_workgroup(A->device);
+    ResShape sh;
+    if (!resident_shape(view, A->cus, max_lds, &sh))
+        return FK_OK;
+    const size_t n = (size_t)A->n, entries = (size_t)A->stored_entries();
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t b_ll = up(n * 32), b_part = up(2 * RES_PART_WORDS * 8), b_dec = 256, b_arr = up(RES_MAX_WG * 4);
+    const size_t b_pub = up(n), b_cnt = up((size_t)sh.groups * 4);
+    const size_t b_list = up((size_t)sh.groups * sh.gcap * 4), b_idx = up(entries * 2);
+    const size_t words = b_ll + b_part + b_dec + b_arr;
+    if (hipMalloc(reinterpret_cast<void **>(&S->res_mem), words + b_pub + b_cnt + b_list + b_idx) != hipSuccess) {
+        (void)hipGetLastError();  // no room: the launch-per-step kernels need none of this
+        S->res_mem = nullptr;
+        return FK_OK;
+    }
+    char *m = S->res_mem;
+    auto take = [&](size_t b) { char *at = m; m += b; return at; };
+    ResArgs &a = S->res_args;
+    a.A = view;
+    a.rows = sh.rows;
+    a.gcap = sh.gcap;
+    a.ll = reinterpret_cast<uint64_t *>(take(b_ll));
+    a.part = reinterpret_cast<uint64_t *>(take(b_part));
+    a.decision = reinterpret_cast<uint64_t *>(take(b_dec));
+    a.arrived = reinterpret_cast<uint32_t *>(take(b_arr));
+    uint8_t *pub = reinterpret_cast<uint8_t *>(take(b_pub));
+    int32_t *cnt = reinterpret_cast<int32_t *>(take(b_cnt)), *list = reinterpret_cast<int32_t *>(take(b_list));
+    uint16_t *idx = reinterpret_cast<uint16_t *>(take(b_idx));
+    HIP_TRY(hipMemsetAsync(S->res_mem, 0, words + b_pub, S->stream));
+    HIP_TRY(launch_res_plan(view, sh, idx, cnt, list, pub, S->stream));
+    std::vector<int32_t> counts;
+    try {
+        counts.resize((size_t)sh.groups);
+    } catch (const std::bad_alloc &) {
+        return fail(FK_E_OOM, "host allocation failed");
+    }
+    HIP_TRY(hipMemcpyAsync(counts.data(), cnt, counts.size() * 4, hipMemcpyDeviceToHost, S->stream));
+    HIP_TRY(hipStreamSynchronize(S->stream));
+    for (int32_t c : counts) {
+        if (c < 0 || c > sh.gcap) {
+            dev_free(S->res_mem);
+            return FK_OK;
+        }
+        sh.ghosts = std::max(sh.ghosts, c);
+    }
+    a.idx = idx;
+    a.gcount = cnt;
+    a.glist = list;
+    a.pub = pub;
+    a.st = S->st;
+    a.ctl = reinterpret_cast<ResCtl *>(S->st + 1);
+    a.hist = S->hist;
+    a.scal = S->scal;
+    const bool two = S->o.method == FK_CG_PIPELINED_1K;
+    for (int i = 0; i < 2; ++i) {
+        a.r[i] = two && i ? S->r2 : S->r;
+        a.p[i] = two && i ? S->p2 : S->p;
+        a.ap[i] = two && i ? S->ap2 : S->ap;
+    }
+    S->res = sh;
+    S->res_words = words;
+    S->resident = true;
+    return FK_OK;
 }
 
 extern "C" fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stream, fk_solver *out)
@@ -1157,7 +1269,7 @@ extern "C" fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stre
         S_TRY(dev_alloc(&S->ap2, n, "Ap (second buffer)"));
     }
     S_TRY(dev_alloc(&S->partials, RED_SCRATCH_DOUBLES, "partials"));
-    S_TRY(dev_alloc(&S->st, 1, "state"));
+    S_TRY(dev_alloc(&S->st, 2, "state"));  // the state, then ResCtl
     // History: entries 0 .. cap-1 are kept (the device drops later ones), cap
     // = min(iterations + 1, FK_HISTORY_DEFAULT or the count asked for), so a
     // large max_iter does not size the buffers.
@@ -1171,11 +1283,11 @@ extern "C" fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stre
         if ((o->flags & FK_FLAG_SCALARS) && !S->mixed && !S->gmres)
             S_TRY(dev_alloc(&S->scal, (size_t)S->hist_cap * 4, "scalars"));
     }
-    S_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_init), 3 * sizeof(DevState), hipHostMallocDefault));
+    S_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_init), 4 * sizeof(DevState), hipHostMallocDefault));
     S_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_status), 2 * sizeof(int32_t), hipHostMallocDefault));
     for (auto &e : S->poll_ev)
         S_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    S_HIP(hipMemsetAsync(S->st, 0, sizeof(DevState), S->stream));
+    S_HIP(hipMemsetAsync(S->st, 0, 2 * sizeof(DevState), S->stream));
     S_HIP(launch_red_init(S->partials, S->stream));
     if (S->gmres) {
         S_HIP(hipMemsetAsync(S->gR, 0, ((size_t)S->gm + 1) * ((size_t)S->gm + 1) * sizeof(double), S->stream));
@@ -1194,6 +1306,8 @@ extern "C" fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stre
     S->small_stage = S->small &&
                      small_staged_lds_bytes(is_bicg_pipelined(o->method), A->n, A->nnz) +
                              SMALL_STATIC_LDS <= max_lds_per_workgroup(A->device);
+    if (!S->small && resident_ok(A, S->o))
+        S_TRY(resident_create(S));
     S_HIP(hipStreamSynchronize(S->stream));
 #undef S_TRY
 #undef S_HIP
@@ -1508,8 +1622,10 @@ static fk_status finish_solve(fk_solver S);
 // Multi-kernel solve: writes the initial state (rtol, max_iter, hist_cap),
 // enqueues the setup and batches of `unroll` iterations with one batch in
 // flight ahead of the one waited for, and leaves the final state in S->last.
+// resume: continue from the state, r, p and A p on the device instead
+// (`done` iterations in).
 static fk_status run_batches(fk_solver S, const double *b, double *x, double rtol, int64_t max_iter,
-                             int32_t hist_cap, bool profile, bool graph)
+                             int32_t hist_cap, bool profile, bool graph, bool resume = false, int64_t done = 0)
 {
     DevState init{};
     init.status = ST_RUNNING;
@@ -1517,10 +1633,11 @@ static fk_status run_batches(fk_solver S, const double *b, double *x, double rto
     init.max_iter = (int32_t)max_iter;
     init.hist_cap = hist_cap;
     S->h_init[0] = init;
-    HIP_TRY(hipMemcpyAsync(S->st, &S->h_init[0], sizeof(DevState), hipMemcpyHostToDevice, S->stream));
+    if (!resume)
+        HIP_TRY(hipMemcpyAsync(S->st, &S->h_init[0], sizeof(DevState), hipMemcpyHostToDevice, S->stream));
 
     const int U = S->o.unroll;
-    int64_t launched = 0;
+    int64_t launched = done;
     int cur = 0;
 
     auto enqueue_batch = [&](int slot, bool with_setup) -> hipError_t {
@@ -1551,7 +1668,7 @@ static fk_status run_batches(fk_solver S, const double *b, double *x, double rto
 
     // A batch slot is reused only after its poll has been waited for (and its
     // profile events harvested).
-    hipError_t e = enqueue_batch(0, true);
+    hipError_t e = enqueue_batch(0, !resume);
     if (e != hipSuccess)
         return fail(FK_E_HIP, "enqueue: %s", hipGetErrorString(e));
     for (;;) {
@@ -1727,6 +1844,57 @@ static fk_status solve_mixed(fk_solver S, const double *b, double *x, bool profi
     return finish_solve(S);
 }
 
+// A resident solve: launches of at most RES_CHUNK iterations until the solve
+// ends.  A launch whose workgroups did not all get onto the chip has written
+// nothing; the launch-per-step kernels go on from where the last one ended.
+static fk_status solve_resident(fk_solver S, const double *b, double *x)
+{
+    DevState init{};
+    init.status = ST_RUNNING;
+    init.rtol = S->o.rtol;
+    init.max_iter = S->o.max_iter;
+    init.hist_cap = S->hist_cap;
+    S->h_init[0] = init;
+    HIP_TRY(hipMemcpyAsync(S->st, &S->h_init[0], sizeof(DevState), hipMemcpyHostToDevice, S->stream));
+    ResArgs a = S->res_args;
+    a.b = b;
+    a.x = x;
+    a.chunk = RES_CHUNK;
+    a.resume = 0;
+    ResCtl ctl{};
+    for (;;) {
+        if (S->res_epoch > UINT32_MAX - 2 * (uint32_t)RES_CHUNK) {  // start the tags again
+            HIP_TRY(launch_clear(reinterpret_cast<double *>(S->res_mem), (int64_t)(S->res_words / 8), S->grid_vec,
+                                 S->stream));
+            S->res_epoch = 1;
+        }
+        a.epoch = S->res_epoch;
+        S->res_epoch += RES_CHUNK + 4;
+        hipError_t e = launch_res_cg(S->res, a, S->stream);
+        if (e != hipSuccess)
+            return fail(FK_E_HIP, "resident solve: %s", hipGetErrorString(e));
+        HIP_TRY(hipMemcpyAsync(&S->h_init[2], S->st, 2 * sizeof(DevState), hipMemcpyDeviceToHost, S->stream));
+        HIP_TRY(hipStreamSynchronize(S->stream));
+        S->last = S->h_init[2];
+        memcpy(&ctl, &S->h_init[3], sizeof ctl);
+        if (ctl.fault == a.epoch)
+            return reduction_fault(S);
+        if (ctl.declined == a.epoch) {
+            fk_status fs = run_batches(S, b, x, S->o.rtol, S->o.max_iter, S->hist_cap, false, false, a.resume != 0,
+                                       a.resume ? S->last.it : 0);
+            return fs != FK_OK ? fs : finish_solve(S);
+        }
+        if (S->last.status != ST_RUNNING)
+            break;
+        a.resume = 1;
+    }
+    if (S->last.status == ST_ZERO_RHS) {
+        HIP_TRY(launch_clear(x, S->n, S->grid_vec, S->stream));
+        HIP_TRY(hipStreamSynchronize(S->stream));
+    }
+    return finish_solve(S);
+}
+
 extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
 {
     if (!S || !b || !x)
@@ -1790,6 +1958,15 @@ extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
         return finish_solve(S);
     }
 
+    if (S->resident) {
+        std::atomic<int> &units = resident_units(S->A->device);
+        if (units.fetch_add(S->res.groups) + S->res.groups <= S->A->cus) {
+            const fk_status fs = solve_resident(S, b, x);
+            units.fetch_sub(S->res.groups);
+            return fs;
+        }
+        units.fetch_sub(S->res.groups);
+    }
     fk_status fs = run_batches(S, b, x, S->o.rtol, S->o.max_iter, S->hist_cap, profile, graph);
     if (fs != FK_OK)
         return fs;

@@ -349,6 +349,49 @@ hipError_t launch_red_init(double *partials, hipStream_t s);
 // hist_cap, everything else zero), written by a one-thread kernel.
 hipError_t launch_state_init(DevState *st, double rtol, int32_t max_iter, int32_t hist_cap, hipStream_t s);
 
+// Resident solvers (fk_resident.hip): a whole solve in one launch of
+// workgroups that are all on the chip together and own their rows.
+constexpr int RES_MAX_WG = 256;
+constexpr int RES_PLAN_WORDS = 12288;  // bitmap of one workgroup's columns (393,216 columns wide)
+constexpr int RES_DIRECT = 64;  // up to here every workgroup collects all partials itself
+// Tagged words per parity: the partials (four double-doubles of 4 words per
+// workgroup), then the rounded sums (two words each) on a line of their own.
+constexpr size_t RES_PART_WORDS = (size_t)16 * RES_MAX_WG + 64;
+struct ResShape {
+    int body = -1;   // threads and rows per thread
+    int rows = 0;    // rows per workgroup (whole slices)
+    int groups = 0;  // workgroups
+    int gcap = 0;    // ghosts that fit the LDS beside the rows
+    int ghosts = 0;  // most ghosts of any workgroup
+};
+struct ResCtl {
+    uint32_t declined, fault;  // the epoch of the launch that was given up / a wait of which ran out
+};
+struct ResArgs {
+    DevCsr A;
+    int32_t rows, gcap, resume, chunk;
+    uint32_t epoch;  // first tag of this launch; it uses at most chunk + 2 of them
+    const uint16_t *idx;
+    const int32_t *gcount, *glist;
+    const uint8_t *pub;
+    const double *b;
+    double *x;
+    double *r[2], *p[2], *ap[2];  // by the parity of the iteration count
+    DevState *st;
+    ResCtl *ctl;
+    double *hist, *scal;
+    uint64_t *ll;        // [2][n][2] tagged words of the published rows
+    uint64_t *part;      // [2][RES_PART_WORDS]
+    uint64_t *decision;  // epoch << 2 | 1 (go) or 2 (declined)
+    uint32_t *arrived;   // [RES_MAX_WG]
+};
+// The shape for a matrix in its current layout; false: not for this solver.
+bool resident_shape(const DevCsr &A, int cus, size_t max_lds, ResShape *out);
+// Ghost lists, entry indices and published rows (pub zeroed beforehand).
+hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, uint16_t *idx, int32_t *gcount, int32_t *glist,
+                           uint8_t *pub, hipStream_t s);
+hipError_t launch_res_cg(const ResShape &sh, const ResArgs &a, hipStream_t s);
+
 // Shared by the C ABI sources: record the thread's error message and
 // return `s`; the device view of a matrix handle.
 fk_status internal_fail(fk_status s, const char *fmt, ...);
