@@ -252,10 +252,11 @@ fk_status fk_csr_stream(fk_csr A, int32_t *streaming, int32_t *sweep);
  * iterates equal those of the multi-kernel path; FK_FLAG_NO_SMALL disables
  * that.  fk_solver_uses_small() tells which path a solver takes.
  *
- * Pipelined CG solves of larger systems (n >= 4096) whose matrix is in a
- * sliced layout of at most seven entries per row and fits the registers and
- * LDS of the chip together with the vectors run as one launch of resident
- * workgroups, with the same iterates (about 40 n bytes more per solver).
+ * Pipelined CG and BiCGStab solves of larger systems (n >= 4096) whose matrix
+ * is in a sliced layout of at most seven entries per row and fits the
+ * registers and LDS of the chip together with the vectors run as one launch of
+ * resident workgroups, with the same iterates (about 40 n bytes more per
+ * solver).
  * FK_FLAG_GRAPH and FK_FLAG_PROFILE, which replay or time the launches of
  * the multi-kernel path, and the streaming mode keep to that path; so does a
  * solve whose workgroups do not find room on the device beside other work.

@@ -1070,34 +1070,41 @@ static std::atomic<int> &resident_units(int device)
 
 // Iterations of one resident launch; longer solves continue in the next.
 constexpr int RES_CHUNK = 8192;
-// Fewest unknowns of a resident solve: below, one workgroup solves alone
-// (2D Poisson, us per iteration, one workgroup / resident / launch per step:
-// 3.4 / 3.8 / 12 at n = 1,024; 9.9 / 3.6 / 12 at 3,969; - / 4.2 / 11.6 at
-// 16,129; - / 6.7 / 15.9 at 261,121; - / 11.8 / 29.4 at 1,000,000; 3D: - /
-// 7.5 / 17.4 at 262,144; - / 13.8 / 23.5 at 512,000).
+constexpr uint32_t RES_TAGS = 2 * RES_CHUNK + 8;  // tags a launch may use: two products an iteration
+// Fewest unknowns of a solve on several resident workgroups; below, one
+// workgroup solves alone.  us per iteration, resident / launch per step:
+// 2D Poisson CG 3.5 / 11.6 at n = 16,129, 6.5 / 15.6 at 261,121, 11.0 / 29.7
+// at 1,000,000; 3D 7.1 / 17.0 at 262,144, 13.2 / 23.4 at 512,000; BiCGStab on
+// 2D convection-diffusion 7.0 / 18.8 at 4,096, 13.6 / 25.7 at 261,121, 31 / 53
+// at 1,048,576.  One workgroup, these kernels / the CSR kernels of
+// fk_kernels.hip: CG 2.0 / 3.5 at n = 1,024, 4.4 / 10.1 at 3,969; BiCGStab
+// 4.2 / 8.0 at 1,024.
 constexpr int64_t RES_MIN_N = 4096;
 
-// Which solves are resident: pipelined CG on a sliced layout of at most
-// seven entries per row whose rows, with their ghosts, fit the chip (the
-// streaming mode is for matrices far beyond it, or asked for).
-static bool resident_ok(fk_csr A, const fk_opts &o)
+// Which solves are resident: the pipelined methods on a sliced layout of at
+// most seven entries per row whose rows, with their ghosts, fit the chip (the
+// streaming mode is for matrices far beyond it, or asked for).  Returns the
+// compute units they may take: one for the single-workgroup solves, 0: not.
+static int resident_units_of(fk_csr A, const fk_opts &o, bool small)
 {
-    if (o.flags & (FK_FLAG_GRAPH | FK_FLAG_PROFILE))  // these time or replay the launches
-        return false;
-    if (o.method != FK_CG_PIPELINED && o.method != FK_CG_PIPELINED_1K)
-        return false;
-    return A->sliced() && !A->streaming() && A->n >= RES_MIN_N;
+    if ((o.flags & FK_FLAG_PROFILE) || (!small && (o.flags & FK_FLAG_GRAPH)))  // these time or replay the launches
+        return 0;
+    if (o.method != FK_CG_PIPELINED && o.method != FK_CG_PIPELINED_1K && !is_bicg_pipelined(o.method))
+        return 0;
+    if (!A->sliced() || A->streaming() || o.max_iter < 1)
+        return 0;
+    return small ? 1 : A->n >= RES_MIN_N ? A->cus : 0;
 }
 
 // The resident workspace of a new solver; leaves S->resident false where the
 // matrix does not fit (or the workspace does not).
-static fk_status resident_create(fk_solver S)
+static fk_status resident_create(fk_solver S, int units)
 {
     fk_csr A = S->A;
     const DevCsr view = A->view();
     const size_t max_lds = max_lds_per_workgroup(A->device);
     ResShape sh;
-    if (!resident_shape(view, A->cus, max_lds, &sh))
+    if (!resident_shape(view, is_bicg(S->o.method), units, max_lds, &sh))
         return FK_OK;
     const size_t n = (size_t)A->n, entries = (size_t)A->stored_entries();
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
@@ -1148,7 +1155,8 @@ static fk_status resident_create(fk_solver S)
     a.ctl = reinterpret_cast<ResCtl *>(S->st + 1);
     a.hist = S->hist;
     a.scal = S->scal;
-    const bool two = S->o.method == FK_CG_PIPELINED_1K;
+    const bool two = S->o.method == FK_CG_PIPELINED_1K || S->o.method == FK_BICGSTAB_PIPELINED_2K;
+    a.rs = S->rs;
     for (int i = 0; i < 2; ++i) {
         a.r[i] = two && i ? S->r2 : S->r;
         a.p[i] = two && i ? S->p2 : S->p;
@@ -1306,8 +1314,8 @@ extern "C" fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stre
     S->small_stage = S->small &&
                      small_staged_lds_bytes(is_bicg_pipelined(o->method), A->n, A->nnz) +
                              SMALL_STATIC_LDS <= max_lds_per_workgroup(A->device);
-    if (!S->small && resident_ok(A, S->o))
-        S_TRY(resident_create(S));
+    if (const int units = resident_units_of(A, S->o, S->small))
+        S_TRY(resident_create(S, units));
     S_HIP(hipStreamSynchronize(S->stream));
 #undef S_TRY
 #undef S_HIP
@@ -1863,14 +1871,14 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
     a.resume = 0;
     ResCtl ctl{};
     for (;;) {
-        if (S->res_epoch > UINT32_MAX - 2 * (uint32_t)RES_CHUNK) {  // start the tags again
+        if (S->res_epoch > UINT32_MAX - RES_TAGS) {  // start the tags again
             HIP_TRY(launch_clear(reinterpret_cast<double *>(S->res_mem), (int64_t)(S->res_words / 8), S->grid_vec,
                                  S->stream));
             S->res_epoch = 1;
         }
         a.epoch = S->res_epoch;
-        S->res_epoch += RES_CHUNK + 4;
-        hipError_t e = launch_res_cg(S->res, a, S->stream);
+        S->res_epoch += RES_TAGS;
+        hipError_t e = launch_resident(S->res, a, S->stream);
         if (e != hipSuccess)
             return fail(FK_E_HIP, "resident solve: %s", hipGetErrorString(e));
         HIP_TRY(hipMemcpyAsync(&S->h_init[2], S->st, 2 * sizeof(DevState), hipMemcpyDeviceToHost, S->stream));
@@ -1918,6 +1926,15 @@ extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
     if (S->gmres)
         return solve_gmres(S, b, x, profile);
 
+    if (S->resident) {
+        std::atomic<int> &units = resident_units(S->A->device);
+        if (units.fetch_add(S->res.groups) + S->res.groups <= S->A->cus) {
+            const fk_status fs = solve_resident(S, b, x);
+            units.fetch_sub(S->res.groups);
+            return fs;
+        }
+        units.fetch_sub(S->res.groups);
+    }
     if (S->small) {
         DevState init{};
         init.status = ST_RUNNING;
@@ -1958,15 +1975,6 @@ extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
         return finish_solve(S);
     }
 
-    if (S->resident) {
-        std::atomic<int> &units = resident_units(S->A->device);
-        if (units.fetch_add(S->res.groups) + S->res.groups <= S->A->cus) {
-            const fk_status fs = solve_resident(S, b, x);
-            units.fetch_sub(S->res.groups);
-            return fs;
-        }
-        units.fetch_sub(S->res.groups);
-    }
     fk_status fs = run_batches(S, b, x, S->o.rtol, S->o.max_iter, S->hist_cap, profile, graph);
     if (fs != FK_OK)
         return fs;

@@ -359,6 +359,7 @@ constexpr int RES_DIRECT = 64;  // up to here every workgroup collects all parti
 constexpr size_t RES_PART_WORDS = (size_t)16 * RES_MAX_WG + 64;
 struct ResShape {
     int body = -1;   // threads and rows per thread
+    bool bicg = false;
     int rows = 0;    // rows per workgroup (whole slices)
     int groups = 0;  // workgroups
     int gcap = 0;    // ghosts that fit the LDS beside the rows
@@ -370,13 +371,14 @@ struct ResCtl {
 struct ResArgs {
     DevCsr A;
     int32_t rows, gcap, resume, chunk;
-    uint32_t epoch;  // first tag of this launch; it uses at most chunk + 2 of them
+    uint32_t epoch;  // first tag of this launch; it uses at most 2 chunk + 4 of them
     const uint16_t *idx;
     const int32_t *gcount, *glist;
     const uint8_t *pub;
     const double *b;
     double *x;
     double *r[2], *p[2], *ap[2];  // by the parity of the iteration count
+    double *rs;                   // BiCGStab: r0*
     DevState *st;
     ResCtl *ctl;
     double *hist, *scal;
@@ -385,12 +387,13 @@ struct ResArgs {
     uint64_t *decision;  // epoch << 2 | 1 (go) or 2 (declined)
     uint32_t *arrived;   // [RES_MAX_WG]
 };
-// The shape for a matrix in its current layout; false: not for this solver.
-bool resident_shape(const DevCsr &A, int cus, size_t max_lds, ResShape *out);
+// The shape for a matrix in its current layout on `units` compute units;
+// false: not for these solvers.
+bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResShape *out);
 // Ghost lists, entry indices and published rows (pub zeroed beforehand).
 hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, uint16_t *idx, int32_t *gcount, int32_t *glist,
                            uint8_t *pub, hipStream_t s);
-hipError_t launch_res_cg(const ResShape &sh, const ResArgs &a, hipStream_t s);
+hipError_t launch_resident(const ResShape &sh, const ResArgs &a, hipStream_t s);
 
 // Shared by the C ABI sources: record the thread's error message and
 // return `s`; the device view of a matrix handle.

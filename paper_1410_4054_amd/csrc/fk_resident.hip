@@ -269,7 +269,7 @@ struct ResShared {
     DevState s;
     dd rows[32][4];  // per row of 16 lanes of each wave: the four dots
     dd psum[RES_MAX_WG / 64][4];
-    double alpha, beta;
+    double alpha, beta, omega, rr_next;
     int status;
     int fault;
     int go;
@@ -329,10 +329,10 @@ __device__ __forceinline__ bool ghost_poll(const uint64_t *ll, const int32_t *gl
 // every workgroup collects for itself: one hand-over.  Above, workgroup 0
 // alone does and hands the rounded sums on: a second hand-over, but 256
 // workgroups reading 24 KB each through the fabric take longer than that
-// (2D Poisson 255^2, 255 workgroups: 8.9 us per iteration).  Waves that
+// (2D Poisson 255^2, 255 workgroups: 8.9 us per iteration, 6.6 with two).  Waves that
 // collect nothing poll the thread's ghost words meanwhile.  Returns false
 // when a wait ran out; ends past a barrier.
-template <int T, int K, typename FIN>
+template <int T, int K, int HALF, typename FIN>
 __device__ __forceinline__ bool all_reduce(dd (&v)[K], ResShared &sh, const ResArgs &a, int g, uint32_t tag,
                                            const uint64_t *ll, const int32_t *gl, int ng, GhostWords &gw, FIN &&fin)
 {
@@ -355,43 +355,57 @@ __device__ __forceinline__ bool all_reduce(dd (&v)[K], ResShared &sh, const ResA
         if constexpr (NR > 16)
             r = dd_add(r, sh.rows[16 + (lane >> 2)][dot]);
         r = wave_quads(r);
-        if (lane < K) {
+        if (G == 1) {  // nobody to hand over to
+            double d[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                d[k] = lane_value(r.hi + r.lo, k);
+            fin(d);
+        } else if (lane < K) {
             store_tagged(part + (size_t)16 * g + 4 * lane, tag, r.hi);
             store_tagged(part + (size_t)16 * g + 4 * lane + 2, tag, r.lo);
         }
     }
+    if (G == 1) {
+        __syncthreads();
+        return true;
+    }
     dd mine{0.0, 0.0};
     if (wave < np) {
-        // lane: dot l & 3 of the members (l >> 2) + 16 i of the wave's 64
+        // lane: dot l & 3 of the members (l >> 2) + 16 i of the wave's 64, HALF of
+        // them at a time (two where registers are short)
         const int m = wave * 64 + (lane >> 2);
-        uint64_t w[16] = {};
-        bool ok = dot >= K;
-        for (int spin = 0;; ++spin) {
-            if (!ok) {
-                ok = true;
+        dd q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (m + 16 * i < G) {
+        for (int h = 0; h < 4; h += HALF) {
+            uint64_t w[4 * HALF] = {};  // members past G and dots past K: sums of zero
+            bool ok = dot >= K;
+            for (int spin = 0;; ++spin) {
+                if (!ok) {
+                    ok = true;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            w[4 * i + j] = load_word(part + (size_t)16 * (m + 16 * i) + 4 * dot + j);
-                    }
+                    for (int i = 0; i < HALF; ++i)
+                        if (m + 16 * (h + i) < G) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (m + 16 * i < G)
-                        ok = ok && tagged(w[4 * i], w[4 * i + 1], tag) && tagged(w[4 * i + 2], w[4 * i + 3], tag);
+                            for (int j = 0; j < 4; ++j)
+                                w[4 * i + j] = load_word(part + (size_t)16 * (m + 16 * (h + i)) + 4 * dot + j);
+                        }
+#pragma unroll
+                    for (int i = 0; i < HALF; ++i)
+                        if (m + 16 * (h + i) < G)
+                            ok = ok && tagged(w[4 * i], w[4 * i + 1], tag) && tagged(w[4 * i + 2], w[4 * i + 3], tag);
+                }
+                if (__builtin_amdgcn_ballot_w64(!ok) == 0)
+                    break;
+                if (spin >= FK_RES_SPIN_LIMIT) {
+                    sh.fault = 1;
+                    break;
+                }
             }
-            if (__builtin_amdgcn_ballot_w64(!ok) == 0)
-                break;
-            if (spin >= FK_RES_SPIN_LIMIT) {
-                sh.fault = 1;
-                break;
-            }
+#pragma unroll
+            for (int i = 0; i < HALF; ++i)
+                q[h + i] = dd{untag(w[4 * i], w[4 * i + 1]), untag(w[4 * i + 2], w[4 * i + 3])};
         }
-        dd q[4];  // members past G and dots past K: words of zero, sums of zero
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            q[i] = dd{untag(w[4 * i], w[4 * i + 1]), untag(w[4 * i + 2], w[4 * i + 3])};
         ghost_load<T>(ll, gl, ng, gw);  // in flight during the sums; checked after the last barrier
         mine = wave_quads(dd_add(dd_add(q[0], q[1]), dd_add(q[2], q[3])));
         if (np > 1 && lane < 4)
@@ -407,8 +421,8 @@ __device__ __forceinline__ bool all_reduce(dd (&v)[K], ResShared &sh, const ResA
     if (wave == 0) {
         double d[K];
         if (np > 0) {
-            for (int w = 1; w < np; ++w)
-                mine = dd_add(mine, sh.psum[w][dot]);
+            if (np > 1)  // lane: dot l & 3 of wave (l >> 2) & 3
+                mine = row_quads((lane >> 2 & 3) < np ? sh.psum[lane >> 2 & 3][dot] : dd{0.0, 0.0});
             const double r = mine.hi + mine.lo;
             if (!direct && lane < K)
                 store_tagged(sums + 2 * lane, tag, r);
@@ -451,6 +465,10 @@ template <int T>
 __device__ __forceinline__ bool everyone_here(ResShared &sh, const ResArgs &a, int g)
 {
     const uint64_t undecided = (uint64_t)a.epoch << 2;
+    if (gridDim.x == 1) {
+        __syncthreads();
+        return true;
+    }
     if (threadIdx.x == 0)
         __hip_atomic_store(a.arrived + g, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool here = true;
@@ -482,32 +500,33 @@ __device__ __forceinline__ bool everyone_here(ResShared &sh, const ResArgs &a, i
 
 // -------------------------------------------------------------------- CG
 
-// Index of the thread's row k among the workgroup's.  With eight rows per
-// thread the compiler must not compute what follows from it (addresses,
+// Index of the thread's row k among the workgroup's.  With four and more rows
+// per thread the compiler must not compute what follows from it (addresses,
 // bounds, unpacked indices of every row) once and hold it over the whole
 // solve: that spills the 256 registers.
 template <int T, int RPT>
 __device__ __forceinline__ int own_row(int k)
 {
     int t = threadIdx.x;
-    if constexpr (RPT >= 8)
+    if constexpr (RPT >= 4)
         asm volatile("" : "+v"(t));
     return k * T + t;
 }
 
-// Values of a row held in LDS instead of registers: two of five with eight
-// rows per thread, whose 256 registers do not hold all of them (all in
+// Values of a row held in LDS instead of registers: two of five (three of
+// seven) with eight rows per thread, whose 256 registers do not hold all of them (all in
 // registers: 202 spilled, 1000^2 Poisson 21 us per iteration).
-constexpr int res_lds_values(int rpt) { return rpt >= 8 ? 2 : 0; }
+constexpr int res_lds_values(int rpt, int w) { return rpt >= 8 ? w == 5 ? 2 : 3 : 0; }
 
 // The workgroup's rows of the matrix: row k of thread t is k T + t, so a
 // wave holds whole slices.
 template <int T, int RPT, int W>
 struct ResRows {
-    static constexpr int WL = res_lds_values(RPT), WR = W - WL;
+    static constexpr int WL = res_lds_values(RPT, W), WR = W - WL;
     double a[RPT][WR];
     double *far;  // values WR .. W-1 of the workgroup's rows, [WL][rows]
     int rows;
+    int zero;     // index of an entry of the gathered vector that holds 0
     uint32_t id[RPT][(W + 1) / 2];  // two 16-bit indices to a word
 
     __device__ __forceinline__ void load(const ResArgs &r, int row0)
@@ -524,7 +543,7 @@ struct ResRows {
             }
 #pragma unroll
             for (int w = 0; w < (W + 1) / 2; ++w)
-                id[k][w] = RES_NONE | RES_NONE << 16;
+                id[k][w] = (uint32_t)zero | (uint32_t)zero << 16;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 const double v = w < width ? r.A.sell_vals[e0 + w * SLICE + lane] : 0.0;
@@ -533,14 +552,17 @@ struct ResRows {
                 else if (off < r.rows)
                     far[(w - WR) * r.rows + k * T + threadIdx.x] = v;
                 if (w < width) {
-                    const uint32_t i = r.idx[e0 + w * SLICE + lane];
+                    uint32_t i = r.idx[e0 + w * SLICE + lane];
+                    i = i == RES_NONE ? (uint32_t)zero : i;
                     id[k][w / 2] = w & 1 ? (id[k][w / 2] & 0xffffu) | i << 16 : (id[k][w / 2] & 0xffff0000u) | i;
                 }
             }
         }
     }
 
-    // Row k times v (own rows, then ghosts), left to right.
+    // Row k times v (own rows, then ghosts, then 0), left to right.  A missing
+    // entry adds 0 * 0, which changes nothing: the sum starts at +0 and,
+    // rounding to nearest, is never -0.
     __device__ __forceinline__ double dot(int k, const double *v) const
     {
         double q = 0.0;
@@ -548,16 +570,14 @@ struct ResRows {
 #pragma unroll
         for (int w = 0; w < (W + 1) / 2; ++w) {
             pair[w] = id[k][w];
-            if constexpr (RPT >= 8)
+            if constexpr (RPT >= 4)
                 asm volatile("" : "+v"(pair[w]));  // see own_row
         }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const uint32_t i = w & 1 ? pair[w / 2] >> 16 : pair[w / 2] & 0xffffu;
-            const bool on = i != RES_NONE;
             const double av = w < WR ? a[k][w < WR ? w : 0] : far[(w - WR) * rows + min(own_row<T, RPT>(k), rows - 1)];
-            const double t = q + av * v[on ? i : 0];
-            q = on ? t : q;
+            q = q + av * v[i];
         }
         return q;
     }
@@ -565,62 +585,105 @@ struct ResRows {
 
 extern __shared__ double res_lds[];
 
+// What the solvers share: the workgroup's place, its ghosts and its matrix.
+// LDS: the vector the next product gathers (own rows, then ghosts), the
+// solver's own ghost vectors, the matrix values that are not in registers.
 template <int T, int RPT, int W>
-__global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
-{
-    __shared__ ResShared sh;
-    const int tid = threadIdx.x;
-    const int g = blockIdx.x;
-    const int n = a.A.n, R = a.rows, row0 = g * R;
-    const int ng = a.gcount[g];
-    const int32_t *gl = a.glist + (size_t)g * a.gcap;
-    double *pv = res_lds;          // p (first x0): own rows, then ghosts
-    double *rg = res_lds + R + ng;  // r of the ghosts
-    // (the last workgroup: workgroup 0 has the sums to collect)
-    double *hist = g == (int)gridDim.x - 1 ? a.hist : nullptr, *scal = hist ? a.scal : nullptr;
-    const int par = a.st->it & 1;  // the buffers a resumed solve left r, p, A p in
-    if (tid == 0) {
-        sh.s = *a.st;
-        sh.fault = 0;
-    }
+struct Res {
+    static constexpr bool BIG = RPT >= 8;
+    const ResArgs &a;
+    ResShared &sh;
+    int tid, g, n, R, row0, ng, par;
+    const int32_t *gl;
+    double *gv;
+    double *hist, *scal;
+    uint32_t tag, pub;
+    GhostWords gw;
     ResRows<T, RPT, W> M;
-    M.far = rg + ng;
-    M.rows = R;
-    M.load(a, row0);
-    constexpr bool P_LDS = RPT >= 8;
-    constexpr bool X_MEM = RPT >= 8;  // x stays in memory (the XCD's L2): read and written once an iteration
-    double rr[RPT], ap[RPT];
-    [[maybe_unused]] double xr[X_MEM ? 1 : RPT];
-    [[maybe_unused]] double pr[P_LDS ? 1 : RPT];
-    uint32_t pub = 0;
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        const int li = k * T + tid, row = row0 + li;
-        rr[k] = ap[k] = 0.0;
-        if constexpr (!X_MEM)
-            xr[k] = li < R && row < n ? a.x[row] : 0.0;
-        if (li < R && row < n) {
-            if (a.pub[row])
-                pub |= 1u << k;
-            if (a.resume) {
-                rr[k] = a.r[par][row];
-                ap[k] = a.ap[par][row];
-            }
+
+    // ghost_vectors: how many the solver keeps behind gv
+    __device__ __forceinline__ Res(const ResArgs &a_, ResShared &sh_, int ghost_vectors) : a(a_), sh(sh_)
+    {
+        tid = threadIdx.x;
+        g = blockIdx.x;
+        n = a.A.n;
+        R = a.rows;
+        row0 = g * R;
+        ng = a.gcount[g];
+        gv = res_lds;
+        // (the last workgroup records: workgroup 0 has the sums to collect)
+        hist = g == (int)gridDim.x - 1 ? a.hist : nullptr;
+        scal = hist ? a.scal : nullptr;
+        par = a.st->it & 1;  // the buffers a resumed solve left r, p, A p in
+        tag = a.epoch;
+        gw = GhostWords{};
+        if (tid == 0) {
+            sh.s = *a.st;
+            sh.fault = 0;
         }
-    }
-    if (!everyone_here<T>(sh, a, g)) {
+        M.zero = R + (1 + ghost_vectors) * ng;
+        M.far = res_lds + M.zero + 1;
+        M.rows = R;
+        gl = a.glist + (size_t)g * a.gcap;
         if (tid == 0)
-            a.ctl->declined = a.epoch;
-        return;
+            gv[M.zero] = 0.0;
+        M.load(a, row0);
+        pub = 0;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k)
+            if (mine(k) && row0 + k * T + tid < n && a.pub[row0 + k * T + tid])
+                pub |= 1u << k;
     }
-    uint32_t tag = a.epoch;
-    auto ll = [&]() { return a.ll + (size_t)(tag & 1u) * 2 * (size_t)n; };
-    GhostWords gw{};
-    // every ghost's word of the current tag: f(j, value)
-    auto each_ghost = [&](auto &&f) -> bool {
+
+    // Whether the wave's slice of row k is the workgroup's (R is whole slices)
+    __device__ __forceinline__ bool mine(int k) const
+    {
+        return k * T + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u)) < R;
+    }
+    // a uniform base and a 32-bit offset: no 64-bit address per row to hold
+    __device__ __forceinline__ double *at(double *v, int li) const
+    {
+        return reinterpret_cast<double *>(reinterpret_cast<char *>(v + row0) + (uint32_t)li * 8u);
+    }
+    __device__ __forceinline__ double get(double *v, int k) const
+    {
+        const int li = own_row<T, RPT>(k);
+        return mine(k) && row0 + li < n ? *at(v, li) : 0.0;
+    }
+    __device__ __forceinline__ void put(double *v, int k, double x) const
+    {
+        const int li = own_row<T, RPT>(k);
+        if (mine(k) && row0 + li < n)
+            *at(v, li) = x;
+    }
+    // the gathered vector's entry of row k
+    __device__ __forceinline__ double own(int k) const
+    {
+        return mine(k) ? gv[own_row<T, RPT>(k)] : 0.0;
+    }
+    __device__ __forceinline__ void set_own(int k, double v) const
+    {
+        if (mine(k))
+            gv[own_row<T, RPT>(k)] = v;
+    }
+    __device__ __forceinline__ const uint64_t *ll() const { return a.ll + (size_t)(tag & 1u) * 2 * (size_t)n; }
+    __device__ __forceinline__ void publish(int k, double v) const
+    {
+        if (pub >> k & 1u)
+            store_tagged(reinterpret_cast<uint64_t *>(
+                             reinterpret_cast<char *>(a.ll + 2 * ((size_t)(tag & 1u) * (size_t)n + (size_t)row0)) +
+                             (uint32_t)own_row<T, RPT>(k) * 16u),
+                         tag, v);
+    }
+    // f(j, value of the current tag) for every ghost j of this thread
+    template <typename F>
+    __device__ __forceinline__ void each_ghost(F &&f)
+    {
         for (int j0 = 0; j0 < ng; j0 += GPT * T) {
-            if (j0 > 0 && !ghost_poll<T>(ll(), gl, ng, tag, gw, j0))
-                return false;
+            if (j0 > 0 && !ghost_poll<T>(ll(), gl, ng, tag, gw, j0)) {
+                sh.fault = 1;
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < GPT; ++i)
                 if (j0 + tid + i * T < ng)
@@ -628,148 +691,174 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
             if (j0 + GPT * T < ng)
                 ghost_load<T>(ll(), gl, ng, gw, j0 + GPT * T);
         }
-        return true;
-    };
-    auto publish = [&](int k, double v) {
-        // a uniform base and a 32-bit offset: no 64-bit address per row held
-        if (pub >> k & 1u)
-            store_tagged(reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(ll() + 2 * (size_t)row0) +
-                                                      (uint32_t)own_row<T, RPT>(k) * 16u),
-                         tag, v);
-    };
-    // p of row k: beside the matrix in a register, or (eight rows) where the
-    // gathers read it
-    auto p_of = [&](int k) {
-        if constexpr (P_LDS) {
-            const int li = own_row<T, RPT>(k);
-            return li < R ? pv[li] : 0.0;
-        } else {
-            return pr[k];
-        }
-    };
-    auto p_set = [&](int k, double v) {
-        if constexpr (!P_LDS)
-            pr[k] = v;
-        const int li = own_row<T, RPT>(k);
-        if (li < R)
-            pv[li] = v;
-    };
-    auto gave_up = [&]() { a.ctl->fault = a.epoch; };
-    // A p and its inner products with p and itself into acc[0], acc[1]
-    auto product = [&](dd &pap, dd &apap) {
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const double q = M.dot(k, pv);
-            ap[k] = q;
-            publish(k, q);
-            dd_fma(pap, q, p_of(k));
-            dd_fma(apap, q, q);
-            if constexpr (P_LDS)
-                __builtin_amdgcn_sched_barrier(0);  // one row's gathers at a time (registers)
-        }
-    };
-
-    if (!a.resume) {
+    }
+    template <int K, typename FIN>
+    __device__ __forceinline__ bool reduce(dd (&v)[K], FIN &&fin)
+    {
+        if (all_reduce<T, K, BIG ? 2 : 4>(v, sh, a, g, tag, ll(), gl, ng, gw, fin))
+            return true;
+        a.ctl->fault = a.epoch;
+        return false;
+    }
+    __device__ __forceinline__ bool start()
+    {
+        if (everyone_here<T>(sh, a, g))
+            return true;
+        if (tid == 0)
+            a.ctl->declined = a.epoch;
+        return false;
+    }
+    // Row k of the product with gv, published.
+    __device__ __forceinline__ double product(int k) const
+    {
+        const double q = M.dot(k, gv);
+        publish(k, q);
+        return q;
+    }
+    // Entries of all rows of a vector kept in memory, requested together (a
+    // load after the store of another row would wait for its own trip).
+    __device__ __forceinline__ void get_all(double *v, double (&out)[RPT]) const
+    {
 #pragma unroll
         for (int k = 0; k < RPT; ++k)
-            if (k * T + tid < R)
-                pv[k * T + tid] = row0 + k * T + tid < n ? a.x[row0 + k * T + tid] : 0.0;
+            out[k] = get(v, k);
+    }
+    // r_0 = b - A x_0 into r, published; its reduction (FIN_SETUP).
+    __device__ __forceinline__ bool residual(double (&r)[RPT])
+    {
+#pragma unroll
+        for (int k = 0; k < RPT; ++k)
+            set_own(k, get(a.x, k));
         for (int j = tid; j < ng; j += T)
-            pv[R + j] = a.x[gl[j]];
+            gv[R + j] = a.x[gl[j]];
         __syncthreads();
         dd acc[2] = {dd{0.0, 0.0}, dd{0.0, 0.0}};
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
-            const int li = k * T + tid, row = row0 + li;
-            const double bi = li < R && row < n ? a.b[row] : 0.0;
-            const double ri = bi - M.dot(k, pv);
-            rr[k] = ri;
-            if constexpr (P_LDS)
-                __builtin_amdgcn_sched_barrier(0);
+            const double bi = get(const_cast<double *>(a.b), k);
+            const double ri = bi - M.dot(k, gv);
+            r[k] = ri;
             publish(k, ri);
             dd_fma(acc[0], ri, ri);
             dd_fma(acc[1], bi, bi);
         }
-        const bool ok = all_reduce<T, 2>(acc, sh, a, g, tag, ll(), gl, ng, gw, [&](const double *d) {
+        return reduce(acc, [&](const double *d) {
             if (tid == 0)
                 finalize(&sh.s, FIN_SETUP, d, 2, hist, scal);
         });
-        if (!ok)
-            return gave_up();
+    }
+};
+
+// Above this sqrt(v) > tol for certain (v the square of a norm), so the
+// test against the tolerance needs the square root only near its end.
+__device__ __forceinline__ double near_of(double tol)
+{
+    return tol > 1e-150 ? tol * tol * (1.0 + 1e-12) : HUGE_VAL;
+}
+
+// The scalars of the loops below: wave 0 of every workgroup computes them from
+// registers, with finalize's expressions, and leaves what the other waves
+// need in LDS; the residual norm's quotient only feeds the history, so it
+// stays off the path between two products.
+
+// ---------------------------------------------------------------------- CG
+
+template <int T, int RPT, int W>
+__global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
+{
+    __shared__ ResShared sh;
+    Res<T, RPT, W> c(a, sh, 1);
+    constexpr bool BIG = Res<T, RPT, W>::BIG;  // p only in LDS
+    double *rg = c.gv + c.R + c.ng;            // r of the ghosts
+    double *pg = c.gv + c.R;                   // p of the ghosts
+    double xr[RPT], rr[RPT], ap[RPT];
+    [[maybe_unused]] double pr[BIG ? 1 : RPT];
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        rr[k] = a.resume ? c.get(a.r[c.par], k) : 0.0;
+        ap[k] = a.resume ? c.get(a.ap[c.par], k) : 0.0;
+        xr[k] = c.get(a.x, k);
+    }
+    if (!c.start())
+        return;
+    auto p_of = [&](int k) {
+        if constexpr (BIG)
+            return c.own(k);
+        else
+            return pr[k];
+    };
+    auto p_set = [&](int k, double v) {
+        if constexpr (!BIG)
+            pr[k] = v;
+        c.set_own(k, v);
+    };
+    auto product = [&](dd &pap, dd &apap) {
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double q = c.product(k);
+            ap[k] = q;
+            dd_fma(pap, q, p_of(k));
+            dd_fma(apap, q, q);
+        }
+    };
+    if (!a.resume) {
+        if (!c.residual(rr))
+            return;
         if (sh.s.status == ST_RUNNING) {
 #pragma unroll
             for (int k = 0; k < RPT; ++k)
                 p_set(k, rr[k]);
-            if (!each_ghost([&](int j, double v) { rg[j] = pv[R + j] = v; }))
-                sh.fault = 1;
+            c.each_ghost([&](int j, double v) { rg[j] = pg[j] = v; });
             __syncthreads();
-            ++tag;
-            dd acc1[2] = {dd{0.0, 0.0}, dd{0.0, 0.0}};
-            product(acc1[0], acc1[1]);
-            if (!all_reduce<T, 2>(acc1, sh, a, g, tag, ll(), gl, ng, gw, [&](const double *d) {
-                    if (tid == 0)
-                        finalize(&sh.s, FIN_CG_ALPHA, d, 2, hist, scal);
+            ++c.tag;
+            dd acc[2] = {dd{0.0, 0.0}, dd{0.0, 0.0}};
+            product(acc[0], acc[1]);
+            if (!c.reduce(acc, [&](const double *d) {
+                    if (c.tid == 0)
+                        finalize(&sh.s, FIN_CG_ALPHA, d, 2, c.hist, c.scal);
                 }))
-                return gave_up();
+                return;
         }
     } else {
         // r, p of the ghosts from where their owners left them; A p again by words
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
-            const int li = k * T + tid;
-            publish(k, ap[k]);
-            p_set(k, li < R && row0 + li < n ? a.p[par][row0 + li] : 0.0);
+            c.publish(k, ap[k]);
+            p_set(k, c.get(a.p[c.par], k));
         }
-        for (int j = tid; j < ng; j += T) {
-            rg[j] = a.r[par][gl[j]];
-            pv[R + j] = a.p[par][gl[j]];
+        for (int j = c.tid; j < c.ng; j += T) {
+            rg[j] = a.r[c.par][c.gl[j]];
+            pg[j] = a.p[c.par][c.gl[j]];
         }
-        if (!ghost_poll<T>(ll(), gl, ng, tag, gw))
+        if (!ghost_poll<T>(c.ll(), c.gl, c.ng, c.tag, c.gw))
             sh.fault = 1;
         __syncthreads();
-        if (sh.fault)
-            return gave_up();
     }
-    // The scalars of the loop: wave 0 of every workgroup computes them from
-    // registers (FIN_CG_RR_ALPHA, the same expressions) and leaves what the
-    // other waves need in LDS; the norm's square root and quotient only feed
-    // the history and, near the tolerance, the test, so they stay off the path
-    // between two products.
-    const double bnorm = sh.s.bnorm, tol = sh.s.tol;
-    const double near = tol > 1e-150 ? tol * tol * (1.0 + 1e-12) : HUGE_VAL;  // above it sqrt(rr) > tol for certain
+    const double bnorm = sh.s.bnorm, tol = sh.s.tol, near = near_of(tol);
     const int max_iter = sh.s.max_iter, it0 = sh.s.it;
     int it = it0, status = sh.s.status;
     double alpha = sh.s.alpha, beta = sh.s.beta, rr_last = sh.s.rr;
     while (status == ST_RUNNING && it - it0 < a.chunk) {
         dd acc[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
         // x_i, r_i, p_i and <r_i, r_i>; r_i, p_i of the ghosts
-        if (!each_ghost([&](int j, double v) {
-                const double ri = rg[j] - alpha * v;
-                rg[j] = ri;
-                pv[R + j] = ri + beta * pv[R + j];
-            }))
-            sh.fault = 1;
+        c.each_ghost([&](int j, double v) {
+            const double ri = rg[j] - alpha * v;
+            rg[j] = ri;
+            pg[j] = ri + beta * pg[j];
+        });
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
             const double pi = p_of(k);
-            if constexpr (!X_MEM) {
-                xr[k] = xr[k] + alpha * pi;
-            } else {
-                const int li = own_row<T, RPT>(k);
-                if (li < R && row0 + li < n) {
-                    double *xp = reinterpret_cast<double *>(reinterpret_cast<char *>(a.x + row0) + (uint32_t)li * 8u);
-                    *xp = *xp + alpha * pi;
-                }
-            }
+            xr[k] = xr[k] + alpha * pi;
             const double ri = rr[k] - alpha * ap[k];
             rr[k] = ri;
             p_set(k, ri + beta * pi);
             dd_fma(acc[2], ri, ri);
         }
         __syncthreads();
-        ++tag;
+        ++c.tag;
         product(acc[0], acc[1]);
-        if (!all_reduce<T, 3>(acc, sh, a, g, tag, ll(), gl, ng, gw, [&](const double *d) {
+        if (!c.reduce(acc, [&](const double *d) {  // FIN_CG_RR_ALPHA
                 const double rr1 = d[2];
                 int st = ST_RUNNING;
                 double al = alpha, be = beta;
@@ -785,25 +874,25 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
                     al = rr1 / d[0];
                     be = al * al * d[1] / rr1 - 1.0;  // Eq. (3)
                 }
-                if (tid == 0) {
+                if (c.tid == 0) {
                     sh.alpha = al;
                     sh.beta = be;
                     sh.status = st;
                     sh.s.rr = rr1;
                 }
             }))
-            return gave_up();
+            return;
         ++it;
         alpha = sh.alpha;
         beta = sh.beta;
         status = sh.status;
         rr_last = sh.s.rr;
-        if (tid == 0 && hist) {
-            put_hist(&sh.s, hist, it, sqrt(rr_last) / bnorm);
-            put_scal(&sh.s, scal, it - 1, 3, rr_last);
+        if (c.tid == 0 && c.hist) {
+            put_hist(&sh.s, c.hist, it, sqrt(rr_last) / bnorm);
+            put_scal(&sh.s, c.scal, it - 1, 3, rr_last);
             if (status == ST_RUNNING) {
-                put_scal(&sh.s, scal, it, 0, alpha);
-                put_scal(&sh.s, scal, it, 1, beta);
+                put_scal(&sh.s, c.scal, it, 0, alpha);
+                put_scal(&sh.s, c.scal, it, 1, beta);
             }
         }
     }
@@ -811,18 +900,14 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
     const int end = it & 1;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-        const int li = k * T + tid, row = row0 + li;
-        if (li < R && row < n) {
-            if constexpr (!X_MEM)
-                a.x[row] = xr[k];
-            if (more) {
-                a.r[end][row] = rr[k];
-                a.p[end][row] = p_of(k);
-                a.ap[end][row] = ap[k];
-            }
+        c.put(a.x, k, xr[k]);
+        if (more) {
+            c.put(a.r[end], k, rr[k]);
+            c.put(a.p[end], k, p_of(k));
+            c.put(a.ap[end], k, ap[k]);
         }
     }
-    if (g == 0 && tid == 0) {
+    if (c.g == 0 && c.tid == 0) {
         if (it > it0) {
             sh.s.it = it;
             sh.s.status = status;
@@ -834,6 +919,284 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
     }
 }
 
+// ---------------------------------------------------------------- BiCGStab
+
+// Algorithm 4 with the two reduction points of the two-kernel schedule: A p
+// with {<Ap,r0*>, <r,r0*>, <r,r>}, then A s with {<As,s>, <As,As>, <As,r0*>,
+// <s,s>}.  A ghost's r and A p share a slot (A p replaces r when s is
+// formed, r the A p when p is); p has one of its own, the gathered vector
+// being s meanwhile.
+template <int T, int RPT, int W>
+__global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
+{
+    __shared__ ResShared sh;
+    Res<T, RPT, W> c(a, sh, 2);
+    constexpr bool BIG = Res<T, RPT, W>::BIG;  // x and r0* in memory (the XCD's L2)
+    double *sg = c.gv + c.R, *pg = sg + c.ng, *rg = pg + c.ng;
+    double rr[RPT], pr[RPT], ap[RPT], as[RPT];
+    [[maybe_unused]] double xr[BIG ? 1 : RPT], rs[BIG ? 1 : RPT];
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        as[k] = 0.0;
+        rr[k] = a.resume ? c.get(a.r[c.par], k) : 0.0;
+        pr[k] = a.resume ? c.get(a.p[c.par], k) : 0.0;
+        ap[k] = a.resume ? c.get(a.ap[c.par], k) : 0.0;
+        if constexpr (!BIG) {
+            xr[k] = c.get(a.x, k);
+            rs[k] = a.resume ? c.get(a.rs, k) : 0.0;
+        }
+    }
+    if (!c.start())
+        return;
+    double mem[RPT];  // r0* or x of the rows, from memory for one phase
+    auto rs_of = [&](int k) {
+        if constexpr (BIG)
+            return mem[k];
+        else
+            return rs[k];
+    };
+    double alpha = 0.0, rho = 0.0;
+    // A p (gathered) and the reduction point after it; dots[1], dots[2] come in
+    auto ap_step = [&](dd (&acc)[3], bool first) -> bool {
+        if constexpr (BIG)
+            c.get_all(a.rs, mem);
+        __syncthreads();
+        ++c.tag;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double q = c.product(k);
+            ap[k] = q;
+            dd_fma(acc[0], q, rs_of(k));
+        }
+        const double rho0 = rho;
+        if (!c.reduce(acc, [&](const double *d) {  // FIN_B_RHO_ALPHA / FIN_B_XRP_ALPHA
+                const double apr = d[0], rh = first ? rho0 : d[1];
+                const bool bad = apr == 0.0 || !isfinite(apr) || rh == 0.0 || !isfinite(rh);
+                if (c.tid == 0) {
+                    sh.s.rho = rh;
+                    if (!first)
+                        sh.s.rr = d[2];
+                    if (!bad)
+                        sh.s.apr = apr;
+                    sh.alpha = bad ? alpha : rh / apr;
+                    sh.status = bad ? ST_BREAKDOWN : ST_RUNNING;
+                }
+            }))
+            return false;
+        alpha = sh.alpha;
+        rho = sh.s.rho;
+        return true;
+    };
+    int status;
+    if (!a.resume) {
+        if (!c.residual(rr))
+            return;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            pr[k] = rr[k];
+            c.put(a.rs, k, rr[k]);  // r0* = r0 (a resumed solve reads it back)
+            if constexpr (!BIG)
+                rs[k] = rr[k];
+        }
+        status = sh.s.status;
+        if (status == ST_RUNNING) {
+            rho = sh.s.rho;
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                c.set_own(k, rr[k]);
+            c.each_ghost([&](int j, double v) { sg[j] = pg[j] = rg[j] = v; });
+            dd acc[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
+            if (!ap_step(acc, true))
+                return;
+            status = sh.status;
+            if (c.tid == 0 && status == ST_RUNNING)
+                put_scal(&sh.s, c.scal, 0, 0, alpha);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < RPT; ++k)
+            c.publish(k, ap[k]);
+        for (int j = c.tid; j < c.ng; j += T) {
+            rg[j] = a.r[c.par][c.gl[j]];
+            pg[j] = a.p[c.par][c.gl[j]];
+        }
+        if (!ghost_poll<T>(c.ll(), c.gl, c.ng, c.tag, c.gw))
+            sh.fault = 1;
+        __syncthreads();
+        alpha = sh.s.alpha;
+        rho = sh.s.rho;
+        status = sh.s.status;
+    }
+    const double bnorm = sh.s.bnorm, tol = sh.s.tol, near = near_of(tol);
+    const int max_iter = sh.s.max_iter, it0 = sh.s.it;
+    int it = it0;
+    double rr_next = 0.0;
+    while (status == ST_RUNNING && it - it0 < a.chunk) {
+        // s = r - alpha A p, A s and its inner products
+        c.each_ghost([&](int j, double v) {
+            sg[j] = rg[j] - alpha * v;
+            rg[j] = v;
+        });
+        dd acc[4] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double si = rr[k] - alpha * ap[k];
+            c.set_own(k, si);
+            dd_fma(acc[3], si, si);
+        }
+        if constexpr (BIG)
+            c.get_all(a.rs, mem);
+        __syncthreads();
+        ++c.tag;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double q = c.product(k);
+            as[k] = q;
+            dd_fma(acc[0], q, c.own(k));
+            dd_fma(acc[1], q, q);
+            dd_fma(acc[2], q, rs_of(k));
+        }
+        if (!c.reduce(acc, [&](const double *d) {  // FIN_B_SS_OMEGA
+                const double ass = d[0], asas = d[1], asr = d[2], ss = d[3];
+                int st = ST_RUNNING;
+                double be = 0.0, om = 0.0, rn = 0.0;
+                if (ss <= near && sqrt(ss) <= tol)
+                    st = ST_HALF;
+                else if (asas == 0.0 || !isfinite(asas) || !isfinite(ass) || !isfinite(asr))
+                    st = ST_BREAKDOWN;
+                else {
+                    be = -asr / sh.s.apr;  // via <s_i, r0*> = 0
+                    om = ass / asas;
+                    rn = ss - 2.0 * om * ass + om * om * asas;
+                    if (!isfinite(rn))
+                        st = ST_FINAL_BREAKDOWN;
+                    else if (rn <= near && sqrt(rn > 0.0 ? rn : 0.0) <= tol)
+                        st = ST_FINAL_CONVERGED;
+                    else if (om == 0.0)
+                        st = ST_FINAL_BREAKDOWN;
+                    else if (it + 1 >= max_iter)
+                        st = ST_FINAL_NOT_CONVERGED;
+                }
+                if (c.tid == 0) {
+                    sh.s.ss = ss;
+                    sh.beta = be;
+                    sh.omega = om;
+                    sh.rr_next = rn;
+                    sh.status = st;
+                }
+            }))
+            return;
+        status = sh.status;
+        if (status == ST_BREAKDOWN)
+            break;
+        const double beta = sh.beta, omega = sh.omega;
+        rr_next = status == ST_HALF ? sh.s.ss : sh.rr_next;
+        if (status == ST_HALF) {
+            if constexpr (BIG)
+                c.get_all(a.x, mem);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                if constexpr (BIG)
+                    c.put(a.x, k, mem[k] + alpha * pr[k]);
+                else
+                    xr[k] = xr[k] + alpha * pr[k];
+            }
+            ++it;
+            break;
+        }
+        // x, r, p of the next iteration; r, p of the ghosts
+        c.each_ghost([&](int j, double v) {
+            const double ri = sg[j] - omega * v;
+            const double pn = ri + beta * (pg[j] - omega * rg[j]);
+            rg[j] = ri;
+            pg[j] = sg[j] = pn;
+        });
+        dd acc3[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
+        if constexpr (BIG) {
+            c.get_all(a.x, mem);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                mem[k] = mem[k] + alpha * pr[k] + omega * c.own(k);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                c.put(a.x, k, mem[k]);
+            c.get_all(a.rs, mem);
+        }
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double si = c.own(k), pi = pr[k];
+            if constexpr (!BIG)
+                xr[k] = xr[k] + alpha * pi + omega * si;
+            const double ri = si - omega * as[k];
+            rr[k] = ri;
+            const double pn = ri + beta * (pi - omega * ap[k]);
+            pr[k] = pn;
+            c.set_own(k, pn);
+            dd_fma(acc3[1], ri, rs_of(k));
+            dd_fma(acc3[2], ri, ri);
+        }
+        ++it;
+        if (c.tid == 0 && c.hist) {
+            put_hist(&sh.s, c.hist, it, sqrt(rr_next > 0.0 ? rr_next : 0.0) / bnorm);
+            put_scal(&sh.s, c.scal, it - 1, 1, beta);
+            put_scal(&sh.s, c.scal, it - 1, 2, omega);
+            put_scal(&sh.s, c.scal, it - 1, 3, rr_next);
+        }
+        if (status != ST_RUNNING) {  // decided: only the last <r,r0*>, <r,r> are left
+            ++c.tag;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                c.publish(k, rr[k]);  // (every reduction is followed by the ghosts' words)
+            if (!c.reduce(acc3, [&](const double *d) {
+                    if (c.tid == 0) {
+                        sh.s.rho = d[1];
+                        sh.s.rr = d[2];
+                    }
+                }))
+                return;
+            break;
+        }
+        if (!ap_step(acc3, false))
+            return;
+        status = sh.status;
+        if (c.tid == 0 && status == ST_RUNNING)
+            put_scal(&sh.s, c.scal, it, 0, alpha);
+    }
+    const bool more = status == ST_RUNNING;  // the chunk ended first
+    const int end = it & 1;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        if constexpr (!BIG)
+            c.put(a.x, k, xr[k]);
+        if (more) {
+            c.put(a.r[end], k, rr[k]);
+            c.put(a.p[end], k, pr[k]);
+            c.put(a.ap[end], k, ap[k]);
+        }
+    }
+    if (c.tid == 0 && c.hist && status == ST_HALF) {
+        put_hist(&sh.s, c.hist, it, sqrt(rr_next) / bnorm);
+        put_scal(&sh.s, c.scal, it - 1, 3, rr_next);
+    }
+    if (c.g == 0 && c.tid == 0) {
+        sh.s.alpha = alpha;
+        sh.s.rho_pub = 0;
+        if (it > it0) {
+            sh.s.it = it;
+            sh.s.beta = sh.beta;
+            sh.s.omega = sh.omega;
+            sh.s.rr_next = sh.rr_next;
+            sh.s.last_rel = sqrt(rr_next > 0.0 ? rr_next : 0.0) / bnorm;
+        }
+        sh.s.status = status == ST_HALF || status == ST_FINAL_CONVERGED ? ST_CONVERGED
+                      : status == ST_FINAL_NOT_CONVERGED                ? ST_NOT_CONVERGED
+                      : status == ST_FINAL_BREAKDOWN                    ? ST_BREAKDOWN
+                                                                        : status;
+        *a.st = sh.s;
+    }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ host
@@ -841,48 +1204,59 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
 namespace {
 
 // Static LDS of the kernels (ResShared) and a margin.
-constexpr size_t RES_STATIC_LDS = 4096;
+constexpr size_t RES_STATIC_LDS = sizeof(ResShared) + 512;
 
 using ResKernel = void (*)(ResArgs);
 
 // Threads and rows per thread: the fewest waves whose threads keep at most
-// eight rows, since every wave joins each reduction.
+// eight rows, since every wave joins each reduction.  Kernels for at most
+// five and at most seven entries per row.
 struct ResBody {
     int threads, rpt;
-    ResKernel cg5, cg7;
+    ResKernel cg[2], bicg[2];
 };
-const ResBody BODIES[] = {
-    {256, 1, k_res_cg<256, 1, 5>, k_res_cg<256, 1, 7>}, {256, 2, k_res_cg<256, 2, 5>, k_res_cg<256, 2, 7>},
-    {512, 2, k_res_cg<512, 2, 5>, k_res_cg<512, 2, 7>}, {512, 4, k_res_cg<512, 4, 5>, k_res_cg<512, 4, 7>},
-    {512, 8, k_res_cg<512, 8, 5>, nullptr},
-};
+#define RES_BODY(T, RPT)                                                                        \
+    {                                                                                           \
+        T, RPT, {k_res_cg<T, RPT, 5>, k_res_cg<T, RPT, 7>}, { k_res_bicg<T, RPT, 5>, k_res_bicg<T, RPT, 7> } \
+    }
+const ResBody BODIES[] = {RES_BODY(256, 1), RES_BODY(256, 2), RES_BODY(512, 2), RES_BODY(512, 4), RES_BODY(512, 8)};
+#undef RES_BODY
+
+int width_class(const DevCsr &A) { return A.max_width <= 5 ? 0 : 1; }
+
+// Doubles of dynamic LDS: the gathered vector, the ghost vectors, the
+// matrix values that are not in registers.
+size_t res_lds_doubles(const ResShape &sh, const DevCsr &A, int ghosts)
+{
+    const int far = res_lds_values(BODIES[sh.body].rpt, width_class(A) ? 7 : 5);
+    return (size_t)sh.rows * (1 + far) + (size_t)(sh.bicg ? 3 : 2) * ghosts + 1;
+}
 
 }  // namespace
 
-bool resident_shape(const DevCsr &A, int cus, size_t max_lds, ResShape *out)
+bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResShape *out)
 {
-    if (A.nslices <= 0 || A.max_width < 1 || A.max_width > 7 || cus < 1)
+    if (A.nslices <= 0 || A.max_width < 1 || A.max_width > 7 || units < 1)
         return false;
-    const int gmax = cus < RES_MAX_WG ? cus : RES_MAX_WG;
+    const int gmax = units < RES_MAX_WG ? units : RES_MAX_WG;
     int64_t rows = ((int64_t)A.nslices + gmax - 1) / gmax * SLICE;
-    if (rows < 256)
+    if (gmax > 1 && rows < 256)
         rows = 256;
     for (int i = 0; i < (int)(sizeof(BODIES) / sizeof(BODIES[0])); ++i) {
-        const ResBody &b = BODIES[i];
-        if ((int64_t)b.threads * b.rpt < rows)
+        if ((int64_t)BODIES[i].threads * BODIES[i].rpt < rows)
             continue;
-        if (A.max_width > 5 && !b.cg7)
+        ResShape sh;
+        sh.body = i;
+        sh.bicg = bicg;
+        sh.rows = (int)rows;
+        sh.groups = (int)(((int64_t)A.n + rows - 1) / rows);
+        const size_t lds = res_lds_doubles(sh, A, 0) * 8 + RES_STATIC_LDS;
+        if (lds > max_lds || sh.groups > RES_MAX_WG)
             return false;
-        const size_t lds = (size_t)rows * 8 * (1 + res_lds_values(b.rpt)) + RES_STATIC_LDS;
-        if (lds + 2048 > max_lds)
-            return false;
-        out->body = i;
-        out->rows = (int)rows;
-        out->groups = (int)(((int64_t)A.n + rows - 1) / rows);
-        out->gcap = (int)((max_lds - lds) / 16);
-        if (out->gcap > 65534 - (int)rows)
-            out->gcap = 65534 - (int)rows;
-        return out->groups <= RES_MAX_WG;
+        const int64_t gcap = (int64_t)((max_lds - lds) / (bicg ? 24 : 16));
+        sh.gcap = (int)(gcap < 65534 - rows ? gcap : 65534 - rows);
+        *out = sh;
+        return true;
     }
     return false;
 }
@@ -894,11 +1268,12 @@ hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, uint16_t *idx, i
     return hipGetLastError();
 }
 
-hipError_t launch_res_cg(const ResShape &sh, const ResArgs &a, hipStream_t s)
+hipError_t launch_resident(const ResShape &sh, const ResArgs &a, hipStream_t s)
 {
     const ResBody &b = BODIES[sh.body];
-    const size_t lds = ((size_t)sh.rows * (1 + res_lds_values(b.rpt)) + 2 * (size_t)sh.ghosts) * 8;
-    hipLaunchKernelGGL(a.A.max_width <= 5 ? b.cg5 : b.cg7, dim3(sh.groups), dim3(b.threads), (uint32_t)lds, s, a);
+    const int w = width_class(a.A);
+    hipLaunchKernelGGL(sh.bicg ? b.bicg[w] : b.cg[w], dim3(sh.groups), dim3(b.threads),
+                       (uint32_t)(res_lds_doubles(sh, a.A, sh.ghosts) * 8), s, a);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """The resident solver (a whole solve in one launch of workgroups that own
 their rows) against the oracle, bit for bit, where its shapes change: the
 last workgroup's remainder, rows per thread 1, 2, 4 and 8 at both thread
-counts, one and two hand-overs per reduction, 5 and 7 entries per row, every
+counts, one workgroup, one and two hand-overs per reduction, 5 and 7 entries per row, every
 sliced layout, ghosts on both sides and more of them than the threads hold
 at once.  Solves run a fixed number of iterations (rtol 0) or to 1e-8."""
 import threading
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
 
 def _check(A, its, layout=None, method="cg_pipelined", x0=None):
     b = P.rhs_uniform(A.n, 11)
-    ref = oracle.solve(A, b, x0=x0, method="cg_pipelined", rtol=0.0, max_iter=its)
+    base = "bicgstab_pipelined" if method.startswith("bicgstab") else "cg_pipelined"
+    ref = oracle.solve(A, b, x0=x0, method=base, rtol=0.0, max_iter=its)
     res, x = gpu_solve(A, b, x0, method=method, rtol=0.0, max_iter=its, layout=layout)
     print(f"[case] n={A.n} {method} {layout} k={res.k}", flush=True)
     assert (res.status, res.k) == (ref.status, ref.k)
@@ -29,21 +30,57 @@ def _check(A, its, layout=None, method="cg_pipelined", x0=None):
 # n one more and one less than whole workgroups (256 rows up to n = 65,536,
 # then n / 256), at the steps of rows per thread (256, 512, 1024, 2048, 4096
 # rows) and at 64 workgroups (16,384), where the hand-over changes
+@pytest.mark.parametrize("method", ["cg_pipelined", "bicgstab_pipelined_2k"])
 @pytest.mark.parametrize("nx,ny", [(4097, 1), (257, 16), (128, 128), (5, 3277), (256, 256), (301, 218), (364, 361),
                                    (512, 512), (513, 512), (725, 723), (1024, 1024)])
-def test_rows_2d(nx, ny, device):
-    _check(P.heat2d(nx, ny=ny), 7)
+def test_rows_2d(nx, ny, method, device):
+    _check(P.heat2d(nx, ny=ny), 5, method=method)
 
 
+@pytest.mark.parametrize("method", ["cg_pipelined", "bicgstab_pipelined"])
 @pytest.mark.parametrize("n", [17, 25, 41, 64, 65, 80])
-def test_rows_3d(n, device):
-    _check(P.poisson3d(n), 5)
+def test_rows_3d(n, method, device):
+    _check(P.poisson3d(n), 4, method=method)
 
 
+# one workgroup: rows per thread 1, 2, 2, 4, 8, whole and partial slices
+@pytest.mark.parametrize("nx,ny", [(1, 1), (15, 17), (16, 16), (257, 1), (32, 32), (45, 45), (41, 50), (64, 64)])
+def test_rows_one_workgroup(nx, ny, device):
+    its = min(6, nx * ny)
+    _check(P.heat2d(nx, ny=ny), its)
+    if nx * ny <= 2048:
+        _check(P.heat2d(nx, ny=ny), its, method="bicgstab_pipelined_2k")
+
+
+@pytest.mark.parametrize("n", [7, 12, 16])
+def test_rows_one_workgroup_3d(n, device):
+    _check(P.poisson3d(n), 6)
+
+
+@pytest.mark.parametrize("method", ["cg_pipelined_1k", "bicgstab_pipelined_2k"])
 @pytest.mark.parametrize("layout", ["sliced", "sliced16", "slots"])
-def test_layouts(layout, device):
+def test_layouts(layout, method, device):
     x0 = np.random.default_rng(2).uniform(-1, 1, 71 * 83)
-    _check(P.heat2d(71, ny=83), 9, layout=layout, method="cg_pipelined_1k", x0=x0)
+    _check(P.heat2d(71, ny=83), 9, layout=layout, method=method, x0=x0)
+
+
+@pytest.mark.parametrize("method", ["bicgstab_pipelined", "bicgstab_pipelined_2k"])
+def test_bicgstab_decisions(method, device):
+    """Every end of a BiCGStab solve: the tolerance on the expanded norm, the
+    half step, the budget after each of the first iterations, b = 0."""
+    A = P.convdiff2d(70)
+    b = P.rhs_uniform(A.n, 5)
+    for rtol, its in ((1e-8, None), (1e-3, None), (0.0, 1), (0.0, 2), (0.0, 3)):
+        ref = oracle.solve(A, b, method="bicgstab_pipelined", rtol=rtol, max_iter=its)
+        res, x = gpu_solve(A, b, method=method, rtol=rtol, max_iter=its)
+        assert (res.status, res.k) == (ref.status, ref.k) and np.array_equal(x, ref.x), (rtol, its)
+        assert np.array_equal(res.history, ref.hist)
+    I4 = P.scaled_identity(5000, 4.0)  # s_0 = 0: the half step ends the solve
+    b = P.rhs_uniform(5000, 6)
+    res, x = gpu_solve(I4, b, method=method)
+    assert (res.status, res.k) == ("converged", 1) and np.array_equal(x, b / 4.0)
+    res, x = gpu_solve(I4, np.zeros(5000), np.ones(5000), method=method)
+    assert (res.status, res.k) == ("converged", 0) and not x.any()
 
 
 def test_scattered_columns(device):
@@ -71,6 +108,12 @@ def test_long_solve_continues(device):
     A = P.heat2d(70, ny=64)
     for method in ("cg_pipelined", "cg_pipelined_1k"):
         _check(A, 8195, method=method)
+    A = P.convdiff2d(65)
+    for method in ("bicgstab_pipelined", "bicgstab_pipelined_2k"):
+        b = P.rhs_uniform(A.n, 11)
+        ref = oracle.solve(A, b, method="bicgstab_pipelined", rtol=0.0, max_iter=8194)
+        res, x = gpu_solve(A, b, method=method, rtol=0.0, max_iter=8194)
+        assert (res.status, res.k) == (ref.status, ref.k) and np.array_equal(x, ref.x, equal_nan=True)
 
 
 def test_concurrent_streams(device):
