@@ -253,9 +253,10 @@ fk_status fk_csr_stream(fk_csr A, int32_t *streaming, int32_t *sweep);
  * that.  fk_solver_uses_small() tells which path a solver takes.
  *
  * Pipelined CG and BiCGStab solves of larger systems (n >= 4096) whose matrix
- * is in a sliced layout of at most seven entries per row and fits the
- * registers and LDS of the chip together with the vectors run as one launch of
- * resident workgroups, with the same iterates (about 40 n bytes more per
+ * is in a sliced layout of at most seven entries per row and whose vectors fit
+ * the registers and LDS of the chip (beyond about a million unknowns CG alone,
+ * up to two million, reading the matrix from the caches) run as one launch of
+ * resident workgroups, with the same iterates (about 50 n bytes more per
  * solver).
  * FK_FLAG_GRAPH and FK_FLAG_PROFILE, which replay or time the launches of
  * the multi-kernel path, and the streaming mode keep to that path; so does a

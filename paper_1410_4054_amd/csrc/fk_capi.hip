@@ -150,6 +150,7 @@ struct fk_csr_s {
     int32_t dg_max_width = 0;    // most slots of any slice
     int32_t sell_max_width = 0;  // most entries per row of any slice (sliced layouts)
     int64_t dg_entries = 0;
+    int64_t stride1 = 0, stride2 = 0;  // slots: the largest offset (2), the largest at most half of it (1)
     int32_t layout = FK_LAYOUT_ROW_BLOCKS;  // layout the products read
     // scratch reduction state for fk_spmv / fk_spmv32
     DevState *st = nullptr;
@@ -489,6 +490,12 @@ static fk_status build_slots(fk_csr A, const int32_t *rp, const int32_t *ci, con
     }
     for (int64_t sl = 0; sl <= ns; ++sl)
         eptr[(size_t)sl] = sptr[(size_t)sl] * SLICE;
+    A->stride1 = A->stride2 = 0;
+    for (int32_t o : offs)
+        A->stride2 = std::max<int64_t>(A->stride2, std::abs((int64_t)o));
+    for (int32_t o : offs)
+        if (2 * std::abs((int64_t)o) <= A->stride2)
+            A->stride1 = std::max<int64_t>(A->stride1, std::abs((int64_t)o));
     for (int64_t r = 0; r < n; ++r) {
         const int64_t sl = r / SLICE, lane = r % SLICE;
         const int32_t *o0 = offs.data() + sptr[(size_t)sl], *o1 = offs.data() + sptr[(size_t)sl + 1];
@@ -1073,10 +1080,10 @@ constexpr int RES_CHUNK = 8192;
 constexpr uint32_t RES_TAGS = 2 * RES_CHUNK + 8;  // tags a launch may use: two products an iteration
 // Fewest unknowns of a solve on several resident workgroups; below, one
 // workgroup solves alone.  us per iteration, resident / launch per step:
-// 2D Poisson CG 3.5 / 11.6 at n = 16,129, 6.5 / 15.6 at 261,121, 11.0 / 29.7
-// at 1,000,000; 3D 7.1 / 17.0 at 262,144, 13.2 / 23.4 at 512,000; BiCGStab on
-// 2D convection-diffusion 7.0 / 18.8 at 4,096, 13.6 / 25.7 at 261,121, 31 / 53
-// at 1,048,576.  One workgroup, these kernels / the CSR kernels of
+// 2D Poisson CG 3.5 / 11.6 at n = 16,129, 5.3 / 15.6 at 261,121, 9.3 / 29.7
+// at 1,000,000; 3D 5.8 / 17.0 at 262,144, 8.9 / 23.4 at 512,000, 37.3 / 50.8 at
+// 2,097,152 (matrix streamed); BiCGStab on 2D convection-diffusion 7.0 / 18.8
+// at 4,096, 11.3 / 26.0 at 261,121, 28.6 / 53 at 1,048,576.  One workgroup, these kernels / the CSR kernels of
 // fk_kernels.hip: CG 2.0 / 3.5 at n = 1,024, 4.4 / 10.1 at 3,969; BiCGStab
 // 4.2 / 8.0 at 1,024.
 constexpr int64_t RES_MIN_N = 4096;
@@ -1096,23 +1103,76 @@ static int resident_units_of(fk_csr A, const fk_opts &o, bool small)
     return small ? 1 : A->n >= RES_MIN_N ? A->cus : 0;
 }
 
+// The slices of each resident workgroup.  Workgroups that own consecutive rows
+// of a grid have two whole planes of ghosts (128^3 Poisson: 16,640 for 8192
+// rows); bricks of D planes by L rows of each have about 2 L + 2 s1 D (4,096).  The
+// strides come from the slot offsets (s2 the largest, s1 the largest at most
+// half of it); the slices are put in brick order and dealt out evenly, so
+// any matrix gets a valid assignment, a grid a good one.
+static void resident_slices(fk_csr A, const ResShape &sh, std::vector<int32_t> &perm, std::vector<int32_t> &owner)
+{
+    const int64_t ns = A->slices(), spw = sh.rows / SLICE;
+    std::vector<int32_t> order((size_t)ns);
+    for (int64_t i = 0; i < ns; ++i)
+        order[(size_t)i] = (int32_t)i;
+    const int64_t s2 = A->stride2, s1 = std::max<int64_t>(A->stride1, 1);
+    // (four slices in a row have few ghosts anyway, and fewer neighbours: 127^2
+    // 3.5 us per iteration, 3.8 in bricks)
+    if (A->slots() && sh.groups > 1 && spw > 4 && s2 > SLICE) {
+        // slices of neighbouring lines are shifted against each other by s2 mod 64
+        const int64_t shift = std::min(s2 % SLICE, SLICE - s2 % SLICE);
+        int64_t best_d = 1, best_l = sh.rows, best = INT64_MAX;
+        for (int64_t d = 1; d * SLICE <= sh.rows; ++d) {
+            const int64_t l = std::min<int64_t>((sh.rows / d + SLICE - 1) / SLICE * SLICE, (s2 + SLICE - 1) / SLICE * SLICE);
+            const int64_t ghosts = 2 * l + (l >= s2 ? 0 : 2 * (s1 + shift) * d);
+            if (ghosts < best) {
+                best = ghosts;
+                best_d = d;
+                best_l = l;
+            }
+        }
+        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+            const int64_t ra = (int64_t)a * SLICE, rb = (int64_t)b * SLICE;
+            const int64_t da = ra / s2 / best_d, db = rb / s2 / best_d;
+            return da != db ? da < db : ra % s2 / best_l < rb % s2 / best_l;
+        });
+    }
+    perm.assign((size_t)sh.groups * spw, -1);
+    owner.resize((size_t)ns);
+    for (int64_t i = 0; i < ns; ++i) {
+        perm[(size_t)i] = order[(size_t)i];
+        owner[(size_t)order[(size_t)i]] = (int32_t)(i / spw << 16 | i % spw);
+    }
+}
+
 // The resident workspace of a new solver; leaves S->resident false where the
 // matrix does not fit (or the workspace does not).
-static fk_status resident_create(fk_solver S, int units)
+static fk_status resident_create(fk_solver S, int units, int first = 0)
 {
     fk_csr A = S->A;
     const DevCsr view = A->view();
     const size_t max_lds = max_lds_per_workgroup(A->device);
     ResShape sh;
-    if (!resident_shape(view, is_bicg(S->o.method), units, max_lds, &sh))
+    if (!resident_shape(view, is_bicg(S->o.method), units, max_lds, first, &sh))
         return FK_OK;
+    std::vector<int32_t> perm, owner, counts;
+    try {
+        resident_slices(A, sh, perm, owner);
+        counts.resize((size_t)sh.groups);
+    } catch (const std::bad_alloc &) {
+        return fail(FK_E_OOM, "host allocation failed");
+    }
     const size_t n = (size_t)A->n, entries = (size_t)A->stored_entries();
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    // the tagged words, zero before the first tag, then the plan
     const size_t b_ll = up(n * 32), b_part = up(2 * RES_PART_WORDS * 8), b_dec = 256, b_arr = up(RES_MAX_WG * 4);
-    const size_t b_pub = up(n), b_cnt = up((size_t)sh.groups * 4);
+    const size_t b_pub = up(n), b_cnt = up(counts.size() * 4);
     const size_t b_list = up((size_t)sh.groups * sh.gcap * 4), b_idx = up(entries * 2);
+    const size_t b_perm = up(perm.size() * 4), b_own = up(owner.size() * 4);
+    const size_t b_idx4 = resident_streams(sh) ? (size_t)A->slices() * SLICE * sizeof(uint4) : 0;
     const size_t words = b_ll + b_part + b_dec + b_arr;
-    if (hipMalloc(reinterpret_cast<void **>(&S->res_mem), words + b_pub + b_cnt + b_list + b_idx) != hipSuccess) {
+    if (hipMalloc(reinterpret_cast<void **>(&S->res_mem),
+                  words + b_pub + b_cnt + b_list + b_idx + b_perm + b_own + b_idx4) != hipSuccess) {
         (void)hipGetLastError();  // no room: the launch-per-step kernels need none of this
         S->res_mem = nullptr;
         return FK_OK;
@@ -1130,23 +1190,26 @@ static fk_status resident_create(fk_solver S, int units)
     uint8_t *pub = reinterpret_cast<uint8_t *>(take(b_pub));
     int32_t *cnt = reinterpret_cast<int32_t *>(take(b_cnt)), *list = reinterpret_cast<int32_t *>(take(b_list));
     uint16_t *idx = reinterpret_cast<uint16_t *>(take(b_idx));
+    int32_t *d_perm = reinterpret_cast<int32_t *>(take(b_perm)), *d_own = reinterpret_cast<int32_t *>(take(b_own));
+    uint4 *idx4 = reinterpret_cast<uint4 *>(take(b_idx4));
     HIP_TRY(hipMemsetAsync(S->res_mem, 0, words + b_pub, S->stream));
-    HIP_TRY(launch_res_plan(view, sh, idx, cnt, list, pub, S->stream));
-    std::vector<int32_t> counts;
-    try {
-        counts.resize((size_t)sh.groups);
-    } catch (const std::bad_alloc &) {
-        return fail(FK_E_OOM, "host allocation failed");
-    }
+    HIP_TRY(hipMemcpyAsync(d_perm, perm.data(), perm.size() * 4, hipMemcpyHostToDevice, S->stream));
+    HIP_TRY(hipMemcpyAsync(d_own, owner.data(), owner.size() * 4, hipMemcpyHostToDevice, S->stream));
+    HIP_TRY(launch_res_plan(view, sh, d_perm, d_own, idx, cnt, list, pub, S->stream));
     HIP_TRY(hipMemcpyAsync(counts.data(), cnt, counts.size() * 4, hipMemcpyDeviceToHost, S->stream));
     HIP_TRY(hipStreamSynchronize(S->stream));
     for (int32_t c : counts) {
-        if (c < 0 || c > sh.gcap) {
+        if (c < 0 || c > sh.gcap) {  // a body with fewer values in LDS has room for more
             dev_free(S->res_mem);
-            return FK_OK;
+            return resident_create(S, units, sh.body + 1);
         }
         sh.ghosts = std::max(sh.ghosts, c);
     }
+    if (b_idx4 > 0) {
+        HIP_TRY(launch_res_pack(view, sh, d_own, cnt, idx, idx4, S->stream));
+        a.idx4 = idx4;
+    }
+    a.perm = d_perm;
     a.idx = idx;
     a.gcount = cnt;
     a.glist = list;

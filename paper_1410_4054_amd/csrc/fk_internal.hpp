@@ -373,6 +373,7 @@ struct ResArgs {
     int32_t rows, gcap, resume, chunk;
     uint32_t epoch;  // first tag of this launch; it uses at most 2 chunk + 4 of them
     const uint16_t *idx;
+    const uint4 *idx4;  // streamed matrices: idx packed, one load per row
     const int32_t *gcount, *glist;
     const uint8_t *pub;
     const double *b;
@@ -386,13 +387,20 @@ struct ResArgs {
     uint64_t *part;      // [2][RES_PART_WORDS]
     uint64_t *decision;  // epoch << 2 | 1 (go) or 2 (declined)
     uint32_t *arrived;   // [RES_MAX_WG]
+    const int32_t *perm;  // [groups][rows / SLICE]: the workgroup's slices, -1: none
 };
-// The shape for a matrix in its current layout on `units` compute units;
-// false: not for these solvers.
-bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResShape *out);
-// Ghost lists, entry indices and published rows (pub zeroed beforehand).
-hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, uint16_t *idx, int32_t *gcount, int32_t *glist,
-                           uint8_t *pub, hipStream_t s);
+// The shape for a matrix in its current layout on `units` compute units, of
+// the bodies from `first` on; false: not for these solvers.
+bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, int first, ResShape *out);
+// Ghost lists, entry indices and published rows (pub zeroed beforehand) for
+// the slices each workgroup owns (perm; owner[slice] = workgroup << 16 | place).
+hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, const int32_t *perm, const int32_t *owner,
+                           uint16_t *idx, int32_t *gcount, int32_t *glist, uint8_t *pub, hipStream_t s);
+// Whether the shape reads the matrix anew for every product, and the packed
+// indices it then needs (after launch_res_plan).
+bool resident_streams(const ResShape &sh);
+hipError_t launch_res_pack(const DevCsr &A, const ResShape &sh, const int32_t *owner, const int32_t *gcount,
+                           const uint16_t *idx, uint4 *out, hipStream_t s);
 hipError_t launch_resident(const ResShape &sh, const ResArgs &a, hipStream_t s);
 
 // Shared by the C ABI sources: record the thread's error message and

@@ -73,36 +73,45 @@ __device__ __forceinline__ int entry_col(const DevCsr &A, int sl, int e0, int k,
 // Workgroup g: its ghosts in ascending order (at most gcap of them are
 // stored), their number (-1: the columns span more than the bitmap) and the
 // 16-bit index of every entry of its slices; pub[c] = 1 for every ghost c.
-__global__ __launch_bounds__(PLAN_T) void k_res_plan(DevCsr A, int rows, int gcap, uint16_t *idx, int32_t *gcount,
+// Slice j of workgroup g is perm[g * spw + j] (-1: none); owner[slice] =
+// g << 16 | j.
+__global__ __launch_bounds__(PLAN_T) void k_res_plan(DevCsr A, int spw, int gcap, const int32_t *perm,
+                                                     const int32_t *owner, uint16_t *idx, int32_t *gcount,
                                                      int32_t *glist, uint8_t *pub)
 {
     __shared__ uint32_t bits[RES_PLAN_WORDS];
     __shared__ uint32_t pre[PLAN_T];
     __shared__ int lo_s, hi_s;
     const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const int row0 = g * rows, row1 = min(A.n, row0 + rows);
-    const int s0 = row0 / SLICE, s1 = (row1 + SLICE - 1) / SLICE;
+    // f(entry, column or -1, local slice) over the workgroup's entries
+    auto entries = [&](auto &&f) {
+        for (int j = tid / 64; j < spw; j += PLAN_T / 64) {
+            const int sl = perm[g * spw + j];
+            if (sl < 0)
+                continue;
+            const int e0 = A.sell_ptr[sl], width = (A.sell_ptr[sl + 1] - e0) / SLICE, row = sl * SLICE + lane;
+            for (int k = 0; k < width; ++k)
+                f(e0 + k * SLICE + lane, row < A.n ? entry_col(A, sl, e0, k, lane, row) : -1);
+        }
+    };
+    auto mine = [&](int c) { return owner[c / SLICE] >> 16 == g; };
     if (tid == 0) {
-        lo_s = row0;
-        hi_s = row1 - 1;
+        lo_s = A.n;
+        hi_s = -1;
     }
     __syncthreads();
-    int lo = row0, hi = row1 - 1;
-    for (int sl = s0 + tid / 64; sl < s1; sl += PLAN_T / 64) {
-        const int e0 = A.sell_ptr[sl], width = (A.sell_ptr[sl + 1] - e0) / SLICE, row = sl * SLICE + lane;
-        for (int k = 0; k < width; ++k) {
-            const int c = row < A.n ? entry_col(A, sl, e0, k, lane, row) : -1;
-            if (c >= 0) {
-                lo = min(lo, c);
-                hi = max(hi, c);
-            }
+    int lo = A.n, hi = -1;
+    entries([&](int, int c) {
+        if (c >= 0 && !mine(c)) {
+            lo = min(lo, c);
+            hi = max(hi, c);
         }
-    }
+    });
     atomicMin(&lo_s, lo);
     atomicMax(&hi_s, hi);
     __syncthreads();
     lo = lo_s;
-    const int64_t span = (int64_t)hi_s - lo + 1;
+    const int64_t span = max((int64_t)hi_s - lo + 1, (int64_t)0);
     if (span > (int64_t)RES_PLAN_WORDS * 32) {
         if (tid == 0)
             gcount[g] = -1;
@@ -112,14 +121,10 @@ __global__ __launch_bounds__(PLAN_T) void k_res_plan(DevCsr A, int rows, int gca
     for (int w = tid; w < nw; w += PLAN_T)
         bits[w] = 0;
     __syncthreads();
-    for (int sl = s0 + tid / 64; sl < s1; sl += PLAN_T / 64) {
-        const int e0 = A.sell_ptr[sl], width = (A.sell_ptr[sl + 1] - e0) / SLICE, row = sl * SLICE + lane;
-        for (int k = 0; k < width; ++k) {
-            const int c = row < A.n ? entry_col(A, sl, e0, k, lane, row) : -1;
-            if (c >= 0 && (c < row0 || c >= row1))
-                atomicOr(&bits[(c - lo) >> 5], 1u << ((c - lo) & 31));
-        }
-    }
+    entries([&](int, int c) {
+        if (c >= 0 && !mine(c))
+            atomicOr(&bits[(c - lo) >> 5], 1u << ((c - lo) & 31));
+    });
     __syncthreads();
     // ghosts before each thread's share of the bitmap
     const int per = (nw + PLAN_T - 1) / PLAN_T;
@@ -147,24 +152,40 @@ __global__ __launch_bounds__(PLAN_T) void k_res_plan(DevCsr A, int rows, int gca
             ++at;
         }
     }
-    for (int sl = s0 + tid / 64; sl < s1; sl += PLAN_T / 64) {
-        const int e0 = A.sell_ptr[sl], width = (A.sell_ptr[sl + 1] - e0) / SLICE, row = sl * SLICE + lane;
-        for (int k = 0; k < width; ++k) {
-            const int c = row < A.n ? entry_col(A, sl, e0, k, lane, row) : -1;
-            uint32_t v = RES_NONE;
-            if (c >= row0 && c < row1) {
-                v = (uint32_t)(c - row0);
-            } else if (c >= 0) {
-                const int w = (c - lo) >> 5, t = w / per;
-                uint32_t r = t > 0 ? pre[t - 1] : 0;
-                for (int u = t * per; u < w; ++u)
-                    r += __popc(bits[u]);
-                r += __popc(bits[w] & ((1u << ((c - lo) & 31)) - 1u));
-                v = (uint32_t)rows + r;
-            }
-            idx[e0 + k * SLICE + lane] = (uint16_t)v;
+    entries([&](int e, int c) {
+        uint32_t v = RES_NONE;
+        if (c >= 0 && mine(c)) {
+            v = (uint32_t)((owner[c / SLICE] & 0xffff) * SLICE + c % SLICE);
+        } else if (c >= 0) {
+            const int w = (c - lo) >> 5, t = w / per;
+            uint32_t r = t > 0 ? pre[t - 1] : 0;
+            for (int u = t * per; u < w; ++u)
+                r += __popc(bits[u]);
+            r += __popc(bits[w] & ((1u << ((c - lo) & 31)) - 1u));
+            v = (uint32_t)(spw * SLICE) + r;
         }
+        idx[e] = (uint16_t)v;
+    });
+}
+
+// Streamed matrices: the indices of a row's entries as four words of two
+// (pads and missing entries: the gathered vector's zero).
+__global__ __launch_bounds__(256) void k_res_pack(DevCsr A, int rows, const int32_t *owner, const int32_t *gcount,
+                                                  const uint16_t *idx, uint4 *out)
+{
+    const int sl = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (sl >= A.nslices)
+        return;
+    const int e0 = A.sell_ptr[sl], width = (A.sell_ptr[sl + 1] - e0) / SLICE;
+    const uint32_t zero = (uint32_t)(rows + 2 * gcount[owner[sl] >> 16]);
+    uint32_t w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t i = k < width ? idx[e0 + k * SLICE + lane] : RES_NONE;
+        w[k] = i == RES_NONE ? zero : i;
     }
+    out[(size_t)sl * SLICE + lane] =
+        uint4{w[0] | w[1] << 16, w[2] | w[3] << 16, w[4] | w[5] << 16, w[6] | w[7] << 16};
 }
 
 // ------------------------------------------------------------- hand-over
@@ -265,6 +286,17 @@ __device__ __forceinline__ dd wave_quads(dd v)
     return dd_add(a, b);
 }
 
+// A sum that is complete here, with many rows per thread: without this the
+// compiler moves the additions of a whole phase to where the sum is used and
+// holds every summand (16 rows: 96 registers spilled; none with it).  With
+// few rows the moved additions fill the gathers' latency.
+template <bool BIG>
+__device__ __forceinline__ void settle(dd &v)
+{
+    if constexpr (BIG)
+        asm volatile("" : "+v"(v.hi), "+v"(v.lo));
+}
+
 struct ResShared {
     DevState s;
     dd rows[32][4];  // per row of 16 lanes of each wave: the four dots
@@ -282,12 +314,14 @@ struct GhostWords {
     uint64_t lo[GPT], hi[GPT];
 };
 
-template <int T>
+template <int T, bool CLEAR = false>
 __device__ __forceinline__ void ghost_load(const uint64_t *ll, const int32_t *gl, int ng, GhostWords &w, int j0 = 0)
 {
 #pragma unroll
     for (int i = 0; i < GPT; ++i) {
         const int j = j0 + (int)threadIdx.x + i * T;
+        if constexpr (CLEAR)
+            w.lo[i] = w.hi[i] = 0;  // (nothing held from the last time)
         if (j < ng) {
             const uint64_t *p = ll + 2 * (size_t)gl[j];
             w.lo[i] = load_word(p);
@@ -406,15 +440,20 @@ __device__ __forceinline__ bool all_reduce(dd (&v)[K], ResShared &sh, const ResA
             for (int i = 0; i < HALF; ++i)
                 q[h + i] = dd{untag(w[4 * i], w[4 * i + 1]), untag(w[4 * i + 2], w[4 * i + 3])};
         }
-        ghost_load<T>(ll, gl, ng, gw);  // in flight during the sums; checked after the last barrier
+        ghost_load<T, HALF < 4>(ll, gl, ng, gw);  // in flight during the sums; checked after the last barrier
         mine = wave_quads(dd_add(dd_add(q[0], q[1]), dd_add(q[2], q[3])));
         if (np > 1 && lane < 4)
             sh.psum[wave][dot] = mine;
-    } else if (wave > 0) {
-        if (!ghost_poll<T>(ll, gl, ng, tag, gw))
+    } else if (HALF < 4) {
+        // (loaded before the first test, so that the last iteration's words need
+        // not be held in registers through the product)
+        ghost_load<T, true>(ll, gl, ng, gw);
+        if (wave > 0 && !ghost_poll<T>(ll, gl, ng, tag, gw))
             sh.fault = 1;
-    } else {
+    } else if (wave == 0) {
         ghost_load<T>(ll, gl, ng, gw);
+    } else if (!ghost_poll<T>(ll, gl, ng, tag, gw)) {
+        sh.fault = 1;
     }
     if (np > 1)
         __syncthreads();
@@ -502,8 +541,8 @@ __device__ __forceinline__ bool everyone_here(ResShared &sh, const ResArgs &a, i
 
 // Index of the thread's row k among the workgroup's.  With four and more rows
 // per thread the compiler must not compute what follows from it (addresses,
-// bounds, unpacked indices of every row) once and hold it over the whole
-// solve: that spills the 256 registers.
+// unpacked indices of every row) once and hold it over the whole solve: that
+// spills the 256 registers.
 template <int T, int RPT>
 __device__ __forceinline__ int own_row(int k)
 {
@@ -513,49 +552,86 @@ __device__ __forceinline__ int own_row(int k)
     return k * T + t;
 }
 
-// Values of a row held in LDS instead of registers: two of five (three of
-// seven) with eight rows per thread, whose 256 registers do not hold all of them (all in
-// registers: 202 spilled, 1000^2 Poisson 21 us per iteration).
-constexpr int res_lds_values(int rpt, int w) { return rpt >= 8 ? w == 5 ? 2 : 3 : 0; }
+// Where the values of a row of w entries live.  Eight rows per thread keep
+// two of five (three of seven) in LDS, since 256 registers do not hold all
+// of them (all in registers: 202 spilled, 1000^2 Poisson 21 us per
+// iteration); sixteen rows read them from the caches for every product.
+constexpr int ST_AHEAD = 1;  // rows requested ahead (1 to 4 measure alike)
+constexpr bool res_streamed(int rpt) { return rpt >= 16; }
+constexpr int res_lds_values(int rpt, int w) { return rpt == 8 ? w == 5 ? 2 : 3 : 0; }
 
-// The workgroup's rows of the matrix: row k of thread t is k T + t, so a
-// wave holds whole slices.
+// The workgroup's rows of the matrix.  Row k of thread t is row t % 64 of the
+// workgroup's slice k T / 64 + t / 64, so a wave holds whole slices.
 template <int T, int RPT, int W>
 struct ResRows {
-    static constexpr int WL = res_lds_values(RPT, W), WR = W - WL;
-    double a[RPT][WR];
+    static constexpr bool STREAM = res_streamed(RPT);
+    static constexpr int WL = res_lds_values(RPT, W), WR = STREAM ? 0 : W - WL;
+    int sl[RPT];  // the slice, -1: none (uniform over the wave)
+    [[maybe_unused]] double a[STREAM ? 1 : RPT][WR > 0 ? WR : 1];
+    [[maybe_unused]] int ext[STREAM ? RPT : 1];  // streamed: first entry / 64 << 3 | width (uniform)
     double *far;  // values WR .. W-1 of the workgroup's rows, [WL][rows]
     int rows;
     int zero;     // index of an entry of the gathered vector that holds 0
-    uint32_t id[RPT][(W + 1) / 2];  // two 16-bit indices to a word
+    uint32_t id[STREAM ? 1 : RPT][(W + 1) / 2];  // two 16-bit indices to a word
 
-    __device__ __forceinline__ void load(const ResArgs &r, int row0)
+    __device__ __forceinline__ void load(const ResArgs &r)
     {
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / SLICE)), lane = threadIdx.x & 63;
+        const int spw = rows / SLICE;
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
-            const int off = k * T + wave * SLICE;
-            const int sl = (row0 + off) / SLICE;
+            const int j = k * (T / SLICE) + wave;
             int e0 = 0, width = 0;
-            if (off < r.rows && sl < r.A.nslices) {
-                e0 = __builtin_amdgcn_readfirstlane(r.A.sell_ptr[sl]);
-                width = (__builtin_amdgcn_readfirstlane(r.A.sell_ptr[sl + 1]) - e0) / SLICE;
+            sl[k] = j < spw ? __builtin_amdgcn_readfirstlane(r.perm[blockIdx.x * spw + j]) : -1;
+            if (sl[k] >= 0) {
+                e0 = __builtin_amdgcn_readfirstlane(r.A.sell_ptr[sl[k]]);
+                width = (__builtin_amdgcn_readfirstlane(r.A.sell_ptr[sl[k] + 1]) - e0) / SLICE;
             }
+            if constexpr (STREAM) {
+                ext[k] = e0 / SLICE << 3 | width;
+            } else {
 #pragma unroll
-            for (int w = 0; w < (W + 1) / 2; ++w)
-                id[k][w] = (uint32_t)zero | (uint32_t)zero << 16;
+                for (int w = 0; w < (W + 1) / 2; ++w)
+                    id[k][w] = (uint32_t)zero | (uint32_t)zero << 16;
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const double v = w < width ? r.A.sell_vals[e0 + w * SLICE + lane] : 0.0;
+                    if (w < WR)
+                        a[k][w < WR ? w : 0] = v;
+                    else if (j < spw)
+                        far[(w - WR) * rows + k * T + threadIdx.x] = v;
+                    if (w < width) {
+                        uint32_t i = r.idx[e0 + w * SLICE + lane];
+                        i = i == RES_NONE ? (uint32_t)zero : i;
+                        id[k][w / 2] = w & 1 ? (id[k][w / 2] & 0xffffu) | i << 16 : (id[k][w / 2] & 0xffff0000u) | i;
+                    }
+                }
+            }
+        }
+    }
+
+    // Streamed: request the values and indices of row k.
+    __device__ __forceinline__ void request(const ResArgs &r, int k, double (&v)[W], uint4 &i) const
+    {
+        int e = ext[k], s = sl[k], lane = threadIdx.x & 63;
+        asm volatile("" : "+s"(e), "+s"(s));  // see own_row
+        asm volatile("" : "+v"(lane));
+        const int width = e & 7;
+        const double *__restrict__ src = r.A.sell_vals + (size_t)(e >> 3) * SLICE;
+        i = uint4{(uint32_t)zero | (uint32_t)zero << 16, (uint32_t)zero | (uint32_t)zero << 16,
+                  (uint32_t)zero | (uint32_t)zero << 16, (uint32_t)zero | (uint32_t)zero << 16};
+        if (s >= 0)
+            i = (r.idx4 + (size_t)s * SLICE)[lane];
+        if (width == W) {
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                v[w] = src[w * SLICE + lane];
+        } else {
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                const double v = w < width ? r.A.sell_vals[e0 + w * SLICE + lane] : 0.0;
-                if (w < WR)
-                    a[k][w < WR ? w : 0] = v;
-                else if (off < r.rows)
-                    far[(w - WR) * r.rows + k * T + threadIdx.x] = v;
-                if (w < width) {
-                    uint32_t i = r.idx[e0 + w * SLICE + lane];
-                    i = i == RES_NONE ? (uint32_t)zero : i;
-                    id[k][w / 2] = w & 1 ? (id[k][w / 2] & 0xffffu) | i << 16 : (id[k][w / 2] & 0xffff0000u) | i;
-                }
+                v[w] = 0.0;
+                if (w < width)
+                    v[w] = src[w * SLICE + lane];
             }
         }
     }
@@ -563,23 +639,57 @@ struct ResRows {
     // Row k times v (own rows, then ghosts, then 0), left to right.  A missing
     // entry adds 0 * 0, which changes nothing: the sum starts at +0 and,
     // rounding to nearest, is never -0.
-    __device__ __forceinline__ double dot(int k, const double *v) const
+    template <typename VAL>
+    __device__ __forceinline__ static double sum(uint32_t (&pair)[(W + 1) / 2], const double *v, VAL &&val)
     {
         double q = 0.0;
-        uint32_t pair[(W + 1) / 2];
-#pragma unroll
-        for (int w = 0; w < (W + 1) / 2; ++w) {
-            pair[w] = id[k][w];
-            if constexpr (RPT >= 4)
-                asm volatile("" : "+v"(pair[w]));  // see own_row
-        }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const uint32_t i = w & 1 ? pair[w / 2] >> 16 : pair[w / 2] & 0xffffu;
-            const double av = w < WR ? a[k][w < WR ? w : 0] : far[(w - WR) * rows + min(own_row<T, RPT>(k), rows - 1)];
-            q = q + av * v[i];
+            q = q + val(w) * v[i];
         }
         return q;
+    }
+    // f(k, row k times v) for every row, in order.
+    template <typename F>
+    __device__ __forceinline__ void product(const ResArgs &r, const double *v, F &&f) const
+    {
+        if constexpr (STREAM) {
+            // requested ST_AHEAD rows ahead
+            double buf[ST_AHEAD + 1][W];
+            uint4 at[ST_AHEAD + 1];
+#pragma unroll
+            for (int k = 0; k < ST_AHEAD; ++k)
+                request(r, k, buf[k], at[k]);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                constexpr int M = ST_AHEAD + 1;
+                if (k + ST_AHEAD < RPT)
+                    request(r, k + ST_AHEAD, buf[(k + ST_AHEAD) % M], at[(k + ST_AHEAD) % M]);
+                const uint4 i = at[k % M];
+                const uint32_t all[4] = {i.x, i.y, i.z, i.w};
+                uint32_t pair[(W + 1) / 2];
+#pragma unroll
+                for (int w = 0; w < (W + 1) / 2; ++w)
+                    pair[w] = all[w];
+                f(k, sum(pair, v, [&](int w) { return buf[k % M][w]; }));
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                uint32_t pair[(W + 1) / 2];
+#pragma unroll
+                for (int w = 0; w < (W + 1) / 2; ++w) {
+                    pair[w] = id[k][w];
+                    if constexpr (RPT >= 4)
+                        asm volatile("" : "+v"(pair[w]));  // see own_row
+                }
+                f(k, sum(pair, v, [&](int w) {
+                      return w < WR ? a[k][w < WR ? w : 0]
+                                    : far[(w - WR) * rows + min(own_row<T, RPT>(k), rows - 1)];
+                  }));
+            }
+        }
     }
 };
 
@@ -593,7 +703,7 @@ struct Res {
     static constexpr bool BIG = RPT >= 8;
     const ResArgs &a;
     ResShared &sh;
-    int tid, g, n, R, row0, ng, par;
+    int tid, g, n, R, ng, par;
     const int32_t *gl;
     double *gv;
     double *hist, *scal;
@@ -608,7 +718,6 @@ struct Res {
         g = blockIdx.x;
         n = a.A.n;
         R = a.rows;
-        row0 = g * R;
         ng = a.gcount[g];
         gv = res_lds;
         // (the last workgroup records: workgroup 0 has the sums to collect)
@@ -627,34 +736,39 @@ struct Res {
         gl = a.glist + (size_t)g * a.gcap;
         if (tid == 0)
             gv[M.zero] = 0.0;
-        M.load(a, row0);
+        M.load(a);
         pub = 0;
 #pragma unroll
         for (int k = 0; k < RPT; ++k)
-            if (mine(k) && row0 + k * T + tid < n && a.pub[row0 + k * T + tid])
+            if (mine(k) && row(k) < n && a.pub[row(k)])
                 pub |= 1u << k;
     }
 
-    // Whether the wave's slice of row k is the workgroup's (R is whole slices)
-    __device__ __forceinline__ bool mine(int k) const
+    // (the slice, like own_row's thread, opaque: no condition held per row)
+    __device__ __forceinline__ int slice(int k) const
     {
-        return k * T + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u)) < R;
+        int s = M.sl[k];
+        if constexpr (RPT >= 4)
+            asm volatile("" : "+s"(s));
+        return s;
     }
+    __device__ __forceinline__ bool mine(int k) const { return slice(k) >= 0; }
+    __device__ __forceinline__ int row(int k) const { return slice(k) * SLICE + (own_row<T, RPT>(0) & 63); }
     // a uniform base and a 32-bit offset: no 64-bit address per row to hold
-    __device__ __forceinline__ double *at(double *v, int li) const
+    __device__ __forceinline__ static double *at(double *v, int i)
     {
-        return reinterpret_cast<double *>(reinterpret_cast<char *>(v + row0) + (uint32_t)li * 8u);
+        return reinterpret_cast<double *>(reinterpret_cast<char *>(v) + (uint32_t)i * 8u);
     }
     __device__ __forceinline__ double get(double *v, int k) const
     {
-        const int li = own_row<T, RPT>(k);
-        return mine(k) && row0 + li < n ? *at(v, li) : 0.0;
+        const int i = row(k);
+        return mine(k) && i < n ? *at(v, i) : 0.0;
     }
     __device__ __forceinline__ void put(double *v, int k, double x) const
     {
-        const int li = own_row<T, RPT>(k);
-        if (mine(k) && row0 + li < n)
-            *at(v, li) = x;
+        const int i = row(k);
+        if (mine(k) && i < n)
+            *at(v, i) = x;
     }
     // the gathered vector's entry of row k
     __device__ __forceinline__ double own(int k) const
@@ -669,10 +783,13 @@ struct Res {
     __device__ __forceinline__ const uint64_t *ll() const { return a.ll + (size_t)(tag & 1u) * 2 * (size_t)n; }
     __device__ __forceinline__ void publish(int k, double v) const
     {
-        if (pub >> k & 1u)
+        uint32_t bits = pub;
+        if constexpr (RPT >= 4)
+            asm volatile("" : "+v"(bits));
+        if (bits >> k & 1u)
             store_tagged(reinterpret_cast<uint64_t *>(
-                             reinterpret_cast<char *>(a.ll + 2 * ((size_t)(tag & 1u) * (size_t)n + (size_t)row0)) +
-                             (uint32_t)own_row<T, RPT>(k) * 16u),
+                             reinterpret_cast<char *>(a.ll + 2 * (size_t)(tag & 1u) * (size_t)n) +
+                             (uint32_t)row(k) * 16u),
                          tag, v);
     }
     // f(j, value of the current tag) for every ghost j of this thread
@@ -708,20 +825,23 @@ struct Res {
             a.ctl->declined = a.epoch;
         return false;
     }
-    // Row k of the product with gv, published.
-    __device__ __forceinline__ double product(int k) const
+    // f(k, row k of the product with gv), the row published.
+    template <typename F>
+    __device__ __forceinline__ void product(F &&f) const
     {
-        const double q = M.dot(k, gv);
-        publish(k, q);
-        return q;
+        M.product(a, gv, [&](int k, double q) {
+            publish(k, q);
+            f(k, q);
+        });
     }
-    // Entries of all rows of a vector kept in memory, requested together (a
-    // load after the store of another row would wait for its own trip).
-    __device__ __forceinline__ void get_all(double *v, double (&out)[RPT]) const
+    // Entries of N rows from k0 of a vector kept in memory, requested together
+    // (a load after the store of another row would wait for its own trip).
+    template <int N>
+    __device__ __forceinline__ void get_rows(double *v, int k0, double (&out)[N]) const
     {
 #pragma unroll
-        for (int k = 0; k < RPT; ++k)
-            out[k] = get(v, k);
+        for (int k = 0; k < N; ++k)
+            out[k] = get(v, k0 + k);
     }
     // r_0 = b - A x_0 into r, published; its reduction (FIN_SETUP).
     __device__ __forceinline__ bool residual(double (&r)[RPT])
@@ -733,15 +853,14 @@ struct Res {
             gv[R + j] = a.x[gl[j]];
         __syncthreads();
         dd acc[2] = {dd{0.0, 0.0}, dd{0.0, 0.0}};
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
+        M.product(a, gv, [&](int k, double q) {
             const double bi = get(const_cast<double *>(a.b), k);
-            const double ri = bi - M.dot(k, gv);
+            const double ri = bi - q;
             r[k] = ri;
             publish(k, ri);
             dd_fma(acc[0], ri, ri);
             dd_fma(acc[1], bi, bi);
-        }
+        });
         return reduce(acc, [&](const double *d) {
             if (tid == 0)
                 finalize(&sh.s, FIN_SETUP, d, 2, hist, scal);
@@ -763,12 +882,77 @@ __device__ __forceinline__ double near_of(double tol)
 
 // ---------------------------------------------------------------------- CG
 
+struct CgScalars {
+    double bnorm, tol, near, alpha, beta, rr;
+    int max_iter, it0, it, status;
+
+    __device__ __forceinline__ explicit CgScalars(const DevState &s)
+        : bnorm(s.bnorm), tol(s.tol), near(near_of(s.tol)), alpha(s.alpha), beta(s.beta), rr(s.rr),
+          max_iter(s.max_iter), it0(s.it), it(s.it), status(s.status)
+    {
+    }
+    // FIN_CG_RR_ALPHA on d = {<p,Ap>, <Ap,Ap>, <r,r>}, by wave 0
+    __device__ __forceinline__ void step(const double *d, ResShared &sh) const
+    {
+        const double rr1 = d[2];
+        int st = ST_RUNNING;
+        double al = alpha, be = beta;
+        if (!isfinite(rr1))
+            st = ST_BREAKDOWN;
+        else if (rr1 <= near && sqrt(rr1) <= tol)
+            st = ST_CONVERGED;
+        else if (it + 1 >= max_iter)
+            st = ST_NOT_CONVERGED;
+        else if (!(d[0] > 0.0) || !isfinite(d[0]) || !isfinite(d[1]))
+            st = ST_BREAKDOWN;
+        else {
+            al = rr1 / d[0];
+            be = al * al * d[1] / rr1 - 1.0;  // Eq. (3)
+        }
+        if (threadIdx.x == 0) {
+            sh.alpha = al;
+            sh.beta = be;
+            sh.status = st;
+            sh.s.rr = rr1;
+        }
+    }
+    // by every thread, after the reduction; records where hist is set
+    __device__ __forceinline__ void take(const ResShared &sh, double *hist, double *scal)
+    {
+        ++it;
+        alpha = sh.alpha;
+        beta = sh.beta;
+        status = sh.status;
+        rr = sh.s.rr;
+        if (threadIdx.x == 0 && hist) {
+            put_hist(&sh.s, hist, it, sqrt(rr) / bnorm);
+            put_scal(&sh.s, scal, it - 1, 3, rr);
+            if (status == ST_RUNNING) {
+                put_scal(&sh.s, scal, it, 0, alpha);
+                put_scal(&sh.s, scal, it, 1, beta);
+            }
+        }
+    }
+    // the solver state, by one thread
+    __device__ __forceinline__ void leave(DevState &s, DevState *out) const
+    {
+        if (it > it0) {
+            s.it = it;
+            s.status = status;
+            s.alpha = alpha;
+            s.beta = beta;
+            s.last_rel = sqrt(rr) / bnorm;
+        }
+        *out = s;
+    }
+};
+
 template <int T, int RPT, int W>
 __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
 {
     __shared__ ResShared sh;
     Res<T, RPT, W> c(a, sh, 1);
-    constexpr bool BIG = Res<T, RPT, W>::BIG;  // p only in LDS
+    constexpr bool BIG = Res<T, RPT, W>::BIG;   // p only in LDS
     double *rg = c.gv + c.R + c.ng;            // r of the ghosts
     double *pg = c.gv + c.R;                   // p of the ghosts
     double xr[RPT], rr[RPT], ap[RPT];
@@ -793,13 +977,13 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
         c.set_own(k, v);
     };
     auto product = [&](dd &pap, dd &apap) {
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const double q = c.product(k);
+        c.product([&](int k, double q) {
             ap[k] = q;
             dd_fma(pap, q, p_of(k));
             dd_fma(apap, q, q);
-        }
+            settle<BIG>(pap);
+            settle<BIG>(apap);
+        });
     };
     if (!a.resume) {
         if (!c.residual(rr))
@@ -830,15 +1014,14 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
             rg[j] = a.r[c.par][c.gl[j]];
             pg[j] = a.p[c.par][c.gl[j]];
         }
+        ghost_load<T>(c.ll(), c.gl, c.ng, c.gw);
         if (!ghost_poll<T>(c.ll(), c.gl, c.ng, c.tag, c.gw))
             sh.fault = 1;
         __syncthreads();
     }
-    const double bnorm = sh.s.bnorm, tol = sh.s.tol, near = near_of(tol);
-    const int max_iter = sh.s.max_iter, it0 = sh.s.it;
-    int it = it0, status = sh.s.status;
-    double alpha = sh.s.alpha, beta = sh.s.beta, rr_last = sh.s.rr;
-    while (status == ST_RUNNING && it - it0 < a.chunk) {
+    CgScalars z(sh.s);
+    while (z.status == ST_RUNNING && z.it - z.it0 < a.chunk) {
+        const double alpha = z.alpha, beta = z.beta;
         dd acc[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
         // x_i, r_i, p_i and <r_i, r_i>; r_i, p_i of the ghosts
         c.each_ghost([&](int j, double v) {
@@ -855,49 +1038,16 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
             p_set(k, ri + beta * pi);
             dd_fma(acc[2], ri, ri);
         }
+        settle<BIG>(acc[2]);
         __syncthreads();
         ++c.tag;
         product(acc[0], acc[1]);
-        if (!c.reduce(acc, [&](const double *d) {  // FIN_CG_RR_ALPHA
-                const double rr1 = d[2];
-                int st = ST_RUNNING;
-                double al = alpha, be = beta;
-                if (!isfinite(rr1))
-                    st = ST_BREAKDOWN;
-                else if (rr1 <= near && sqrt(rr1) <= tol)
-                    st = ST_CONVERGED;
-                else if (it + 1 >= max_iter)
-                    st = ST_NOT_CONVERGED;
-                else if (!(d[0] > 0.0) || !isfinite(d[0]) || !isfinite(d[1]))
-                    st = ST_BREAKDOWN;
-                else {
-                    al = rr1 / d[0];
-                    be = al * al * d[1] / rr1 - 1.0;  // Eq. (3)
-                }
-                if (c.tid == 0) {
-                    sh.alpha = al;
-                    sh.beta = be;
-                    sh.status = st;
-                    sh.s.rr = rr1;
-                }
-            }))
+        if (!c.reduce(acc, [&](const double *d) { z.step(d, sh); }))
             return;
-        ++it;
-        alpha = sh.alpha;
-        beta = sh.beta;
-        status = sh.status;
-        rr_last = sh.s.rr;
-        if (c.tid == 0 && c.hist) {
-            put_hist(&sh.s, c.hist, it, sqrt(rr_last) / bnorm);
-            put_scal(&sh.s, c.scal, it - 1, 3, rr_last);
-            if (status == ST_RUNNING) {
-                put_scal(&sh.s, c.scal, it, 0, alpha);
-                put_scal(&sh.s, c.scal, it, 1, beta);
-            }
-        }
+        z.take(sh, c.hist, c.scal);
     }
-    const bool more = status == ST_RUNNING;  // the chunk ended first
-    const int end = it & 1;
+    const bool more = z.status == ST_RUNNING;  // the chunk ended first
+    const int end = z.it & 1;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
         c.put(a.x, k, xr[k]);
@@ -907,16 +1057,8 @@ __global__ __launch_bounds__(T) void k_res_cg(ResArgs a)
             c.put(a.ap[end], k, ap[k]);
         }
     }
-    if (c.g == 0 && c.tid == 0) {
-        if (it > it0) {
-            sh.s.it = it;
-            sh.s.status = status;
-            sh.s.alpha = alpha;
-            sh.s.beta = beta;
-            sh.s.last_rel = sqrt(rr_last) / bnorm;
-        }
-        *a.st = sh.s;
-    }
+    if (c.g == 0 && c.tid == 0)
+        z.leave(sh.s, a.st);
 }
 
 // ---------------------------------------------------------------- BiCGStab
@@ -959,15 +1101,14 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
     // A p (gathered) and the reduction point after it; dots[1], dots[2] come in
     auto ap_step = [&](dd (&acc)[3], bool first) -> bool {
         if constexpr (BIG)
-            c.get_all(a.rs, mem);
+            c.get_rows(a.rs, 0, mem);
         __syncthreads();
         ++c.tag;
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const double q = c.product(k);
+        c.product([&](int k, double q) {
             ap[k] = q;
             dd_fma(acc[0], q, rs_of(k));
-        }
+            settle<BIG>(acc[0]);
+        });
         const double rho0 = rho;
         if (!c.reduce(acc, [&](const double *d) {  // FIN_B_RHO_ALPHA / FIN_B_XRP_ALPHA
                 const double apr = d[0], rh = first ? rho0 : d[1];
@@ -1020,6 +1161,7 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
             rg[j] = a.r[c.par][c.gl[j]];
             pg[j] = a.p[c.par][c.gl[j]];
         }
+        ghost_load<T>(c.ll(), c.gl, c.ng, c.gw);
         if (!ghost_poll<T>(c.ll(), c.gl, c.ng, c.tag, c.gw))
             sh.fault = 1;
         __syncthreads();
@@ -1044,18 +1186,20 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
             c.set_own(k, si);
             dd_fma(acc[3], si, si);
         }
+        settle<BIG>(acc[3]);
         if constexpr (BIG)
-            c.get_all(a.rs, mem);
+            c.get_rows(a.rs, 0, mem);
         __syncthreads();
         ++c.tag;
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const double q = c.product(k);
+        c.product([&](int k, double q) {
             as[k] = q;
             dd_fma(acc[0], q, c.own(k));
             dd_fma(acc[1], q, q);
             dd_fma(acc[2], q, rs_of(k));
-        }
+            settle<BIG>(acc[0]);
+            settle<BIG>(acc[1]);
+            settle<BIG>(acc[2]);
+        });
         if (!c.reduce(acc, [&](const double *d) {  // FIN_B_SS_OMEGA
                 const double ass = d[0], asas = d[1], asr = d[2], ss = d[3];
                 int st = ST_RUNNING;
@@ -1093,7 +1237,7 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
         rr_next = status == ST_HALF ? sh.s.ss : sh.rr_next;
         if (status == ST_HALF) {
             if constexpr (BIG)
-                c.get_all(a.x, mem);
+                c.get_rows(a.x, 0, mem);
 #pragma unroll
             for (int k = 0; k < RPT; ++k) {
                 if constexpr (BIG)
@@ -1113,14 +1257,14 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
         });
         dd acc3[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
         if constexpr (BIG) {
-            c.get_all(a.x, mem);
+            c.get_rows(a.x, 0, mem);
 #pragma unroll
             for (int k = 0; k < RPT; ++k)
                 mem[k] = mem[k] + alpha * pr[k] + omega * c.own(k);
 #pragma unroll
             for (int k = 0; k < RPT; ++k)
                 c.put(a.x, k, mem[k]);
-            c.get_all(a.rs, mem);
+            c.get_rows(a.rs, 0, mem);
         }
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
@@ -1135,6 +1279,8 @@ __global__ __launch_bounds__(T) void k_res_bicg(ResArgs a)
             dd_fma(acc3[1], ri, rs_of(k));
             dd_fma(acc3[2], ri, ri);
         }
+        settle<BIG>(acc3[1]);
+        settle<BIG>(acc3[2]);
         ++it;
         if (c.tid == 0 && c.hist) {
             put_hist(&sh.s, c.hist, it, sqrt(rr_next > 0.0 ? rr_next : 0.0) / bnorm);
@@ -1219,7 +1365,8 @@ struct ResBody {
     {                                                                                           \
         T, RPT, {k_res_cg<T, RPT, 5>, k_res_cg<T, RPT, 7>}, { k_res_bicg<T, RPT, 5>, k_res_bicg<T, RPT, 7> } \
     }
-const ResBody BODIES[] = {RES_BODY(256, 1), RES_BODY(256, 2), RES_BODY(512, 2), RES_BODY(512, 4), RES_BODY(512, 8)};
+const ResBody BODIES[] = {RES_BODY(256, 1), RES_BODY(256, 2), RES_BODY(512, 2), RES_BODY(512, 4), RES_BODY(512, 8),
+                          {512, 16, {k_res_cg<512, 16, 5>, k_res_cg<512, 16, 7>}, {nullptr, nullptr}}};
 #undef RES_BODY
 
 int width_class(const DevCsr &A) { return A.max_width <= 5 ? 0 : 1; }
@@ -1234,7 +1381,7 @@ size_t res_lds_doubles(const ResShape &sh, const DevCsr &A, int ghosts)
 
 }  // namespace
 
-bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResShape *out)
+bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, int first, ResShape *out)
 {
     if (A.nslices <= 0 || A.max_width < 1 || A.max_width > 7 || units < 1)
         return false;
@@ -1242,9 +1389,11 @@ bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResSh
     int64_t rows = ((int64_t)A.nslices + gmax - 1) / gmax * SLICE;
     if (gmax > 1 && rows < 256)
         rows = 256;
-    for (int i = 0; i < (int)(sizeof(BODIES) / sizeof(BODIES[0])); ++i) {
+    for (int i = first; i < (int)(sizeof(BODIES) / sizeof(BODIES[0])); ++i) {
         if ((int64_t)BODIES[i].threads * BODIES[i].rpt < rows)
             continue;
+        if (bicg && !BODIES[i].bicg[0])
+            return false;
         ResShape sh;
         sh.body = i;
         sh.bicg = bicg;
@@ -1261,17 +1410,27 @@ bool resident_shape(const DevCsr &A, bool bicg, int units, size_t max_lds, ResSh
     return false;
 }
 
-hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, uint16_t *idx, int32_t *gcount, int32_t *glist,
-                           uint8_t *pub, hipStream_t s)
+hipError_t launch_res_plan(const DevCsr &A, const ResShape &sh, const int32_t *perm, const int32_t *owner,
+                           uint16_t *idx, int32_t *gcount, int32_t *glist, uint8_t *pub, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_res_plan, dim3(sh.groups), dim3(PLAN_T), 0, s, A, sh.rows, sh.gcap, idx, gcount, glist, pub);
+    hipLaunchKernelGGL(k_res_plan, dim3(sh.groups), dim3(PLAN_T), 0, s, A, sh.rows / SLICE, sh.gcap, perm, owner, idx,
+                       gcount, glist, pub);
+    return hipGetLastError();
+}
+
+bool resident_streams(const ResShape &sh) { return res_streamed(BODIES[sh.body].rpt); }
+
+hipError_t launch_res_pack(const DevCsr &A, const ResShape &sh, const int32_t *owner, const int32_t *gcount,
+                           const uint16_t *idx, uint4 *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_res_pack, dim3((A.nslices + 3) / 4), dim3(256), 0, s, A, sh.rows, owner, gcount, idx, out);
     return hipGetLastError();
 }
 
 hipError_t launch_resident(const ResShape &sh, const ResArgs &a, hipStream_t s)
 {
-    const ResBody &b = BODIES[sh.body];
     const int w = width_class(a.A);
+    const ResBody &b = BODIES[sh.body];
     hipLaunchKernelGGL(sh.bicg ? b.bicg[w] : b.cg[w], dim3(sh.groups), dim3(b.threads),
                        (uint32_t)(res_lds_doubles(sh, a.A, sh.ghosts) * 8), s, a);
     return hipGetLastError();

@@ -1,6 +1,6 @@
 """The resident solver (a whole solve in one launch of workgroups that own
 their rows) against the oracle, bit for bit, where its shapes change: the
-last workgroup's remainder, rows per thread 1, 2, 4 and 8 at both thread
+last workgroup's remainder, rows per thread 1 to 16 at both thread
 counts, one workgroup, one and two hand-overs per reduction, 5 and 7 entries per row, every
 sliced layout, ghosts on both sides and more of them than the threads hold
 at once.  Solves run a fixed number of iterations (rtol 0) or to 1e-8."""
@@ -41,6 +41,15 @@ def test_rows_2d(nx, ny, method, device):
 @pytest.mark.parametrize("n", [17, 25, 41, 64, 65, 80])
 def test_rows_3d(n, method, device):
     _check(P.poisson3d(n), 4, method=method)
+
+
+# the matrix streamed (more than 4096 rows per workgroup, or more ghosts than
+# fit beside 4096), bricks that do not divide the grid
+@pytest.mark.parametrize("A", [lambda: P.heat2d(1025, ny=1024), lambda: P.heat2d(777, ny=2001),
+                               lambda: P.poisson3d(100), lambda: P.poisson3d(103)],
+                         ids=["1025x1024", "777x2001", "100^3", "103^3"])
+def test_streamed(A, device):
+    _check(A(), 4)
 
 
 # one workgroup: rows per thread 1, 2, 2, 4, 8, whole and partial slices
