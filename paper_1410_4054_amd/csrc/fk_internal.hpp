@@ -141,6 +141,9 @@ struct RedArgs {
     // partials of `kpub` dots (0: none), appended after the kernel's own dots.
     int32_t npub = 0;
     int32_t kpub = 0;
+    // Pinned host memory (or null): the rounded dots [KMAX], then 1.0 once
+    // they are there.
+    double *host = nullptr;
 };
 
 // Rows per slice of the sliced layout: one wave64, one row per lane.

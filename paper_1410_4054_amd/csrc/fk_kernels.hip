@@ -410,6 +410,11 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
         for (int k = 0; k < KT; ++k)
             d[k] = ACC::round(acc[k]);
         finalize(red.st, red.fin, d, kt, red.hist, red.scal);
+        if (red.host) {
+            for (int k = 0; k < kt; ++k)
+                red.host[k] = d[k];
+            red.host[KMAX] = 1.0;
+        }
     }
 }
 
