@@ -329,9 +329,10 @@ hipError_t launch_gm_normalize(int64_t n, double *v, const double *r, int i, int
 // r -= xi_i v_i (the classical form's residual update)
 hipError_t launch_gm_rupdate(int64_t n, double *r, const double *v, int i, const double *R, DevState *st,
                              uint32_t run_mask, int grid, hipStream_t s);
-// x += rho0 (eta_1 v_0 + sum_{j=2}^{used} eta_j v_{j-1})
-hipError_t launch_gm_xupdate(int64_t n, double *x, const double *V, const double *eta, int used,
-                             const DevState *st, int grid, hipStream_t s);
+// After a cycle (ST_CYCLE_DONE): R eta = xi, then
+// x += rho0 (eta_1 v_0 + sum_{j=2}^{used} eta_j v_{j-1}), then running again.
+hipError_t launch_gm_cycle_end(int64_t n, double *x, const double *V, const double *R, int m1, double *eta,
+                               DevState *st, int grid, hipStream_t s);
 
 // Single-workgroup solver (whole solve in one launch) for small systems.
 // Rows per thread: 1, 2, 4 or 8 (0 = too large); LDS bytes it needs.

@@ -1840,13 +1840,48 @@ __global__ __launch_bounds__(WG) void k_gm_rupdate(int64_t n, double *__restrict
         r[t] = r[t] - xi * v[t];
 }
 
+// End of a cycle (status ST_CYCLE_DONE): R eta = xi by back substitution on
+// one thread, from R staged in LDS: 435 dependent steps for 30 columns, 14
+// us, where reading R back, solving on the host and sending eta left the
+// device idle for 75 us per cycle.  A cycle without a step is a breakdown, and
+// a reduction that gave up ends the solve here at the latest.
+__global__ __launch_bounds__(WG) void k_gm_eta(const double *__restrict__ R, int m1, double *eta, DevState *st,
+                                                uint32_t mask)
+{
+    __shared__ double lds[(GM_MAX + 1) * (GM_MAX + 1)];
+    __shared__ double e[GM_MAX + 1];
+    if (!runs_mask(st, mask))
+        return;
+    const int used = st->gi - 1;
+    if (used < 1 || st->red_fault) {
+        if (threadIdx.x == 0)
+            st->status = ST_BREAKDOWN;
+        return;
+    }
+    for (int i = threadIdx.x; i < m1 * m1; i += WG)
+        lds[i] = R[i];
+    __syncthreads();
+    if (threadIdx.x != 0)
+        return;
+    for (int i = used; i >= 1; --i) {
+        double s = lds[i];
+        for (int j = i + 1; j <= used; ++j)
+            s = s - lds[i * m1 + j] * e[j];
+        e[i] = s / lds[i * m1 + i];
+        eta[i] = e[i];
+    }
+}
+
 // x += rho0 (eta_1 v_0 + sum_{j=2}^{used} eta_j v_{j-1}), the sum in j order.
 __global__ __launch_bounds__(WG) void k_gm_xupdate(int64_t n, double *__restrict__ x,
                                                     const double *__restrict__ V,
-                                                    const double *__restrict__ eta, int used,
-                                                    const DevState *st)
+                                                    const double *__restrict__ eta, const DevState *st,
+                                                    uint32_t mask)
 {
+    if (!runs_mask(st, mask))
+        return;
     const double rho0 = st->rho0;
+    const int used = st->gi - 1;
     const int64_t stride = (int64_t)gridDim.x * WG;
     for (int64_t t = (int64_t)blockIdx.x * WG + threadIdx.x; t < n; t += stride) {
         double s = eta[1] * V[t];
@@ -1854,6 +1889,13 @@ __global__ __launch_bounds__(WG) void k_gm_xupdate(int64_t n, double *__restrict
             s = s + eta[j] * V[(size_t)(j - 1) * n + t];
         x[t] = x[t] + rho0 * s;
     }
+}
+
+// The next cycle may run.
+__global__ __launch_bounds__(64) void k_gm_next(DevState *st, uint32_t mask)
+{
+    if (threadIdx.x == 0 && runs_mask(st, mask))
+        st->status = ST_RUNNING;
 }
 
 // ------------------------------------------- single-workgroup solver
@@ -2474,10 +2516,16 @@ hipError_t launch_gm_rupdate(int64_t n, double *r, const double *v, int i, const
     return launch(k_gm_rupdate, grid, WG, s, n, r, v, i, R, st, run_mask);
 }
 
-hipError_t launch_gm_xupdate(int64_t n, double *x, const double *V, const double *eta, int used,
-                             const DevState *st, int grid, hipStream_t s)
+hipError_t launch_gm_cycle_end(int64_t n, double *x, const double *V, const double *R, int m1, double *eta,
+                               DevState *st, int grid, hipStream_t s)
 {
-    return launch(k_gm_xupdate, grid, WG, s, n, x, V, eta, used, st);
+    constexpr uint32_t mask = 1u << ST_CYCLE_DONE;
+    hipError_t e = launch(k_gm_eta, 1, WG, s, R, m1, eta, st, mask);
+    if (e == hipSuccess)
+        e = launch(k_gm_xupdate, grid, WG, s, n, x, V, eta, st, mask);
+    if (e == hipSuccess)
+        e = launch(k_gm_next, 1, 64, s, st, mask);
+    return e;
 }
 
 hipError_t launch_residual32(const DevCsr &A, const double *b, const double *x, float *r32,

@@ -122,3 +122,26 @@ def test_gmres_full_size_fixed(method, device):
     print(f"\n[case] convdiff2d_1024 {method} 60 iterations", flush=True)
     res, x, ref = run(A, b, x0, method, 30, rtol=0.0, max_iter=60)
     assert_same(res, x, ref, "1024^2")
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 8, 9, 64])
+def test_gmres_cycles_in_pieces(m, device):
+    """Restart lengths at the edges of the pieces that a cycle is enqueued in
+    (2 steps, then 6 at a time) and the longest one, with solves that end
+    inside a piece, at its end and one step into the next, and a second solve
+    on the same solver that starts where a cycle was cut short."""
+    A, b, _ = P.workload("convdiff2d_32")
+    x0 = np.random.default_rng(3).uniform(-1, 1, A.n)
+    for method in METHODS:
+        for k in sorted({1, 2, 3, 8, 9, m, m + 1, m + 3}):
+            print(f"\n[case] {method} m={m} k={k}", flush=True)
+            res, x, ref = run(A, b, x0, method, m, rtol=0.0, max_iter=k)
+            assert_same(res, x, ref, f"{method} m={m} k={k}")
+    ref = oracle.solve_gmres(A, b, x0=np.zeros(A.n), m=m, rtol=1e-4)
+    S = fk.Solver(fk.Matrix(A), method="gmres_pipelined", rtol=1e-4, restart=m)
+    bd = dev(b)
+    for _ in range(2):
+        xd = dev(np.zeros(A.n))
+        S.solve(bd, xd)
+        assert S.iterations() == ref.k
+        assert np.array_equal(host(xd), ref.x)
