@@ -102,6 +102,58 @@ __device__ __forceinline__ float wave_sum(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// a and b with their halves exchanged: a keeps its lower half of the lanes
+// (SWAP 32) or its even rows of 16 (SWAP 16) and takes b's there in the rest,
+// b the other way round.
+template <int SWAP>
+__device__ __forceinline__ void dd_swap(dd &a, dd &b)
+{
+    const auto one = [](double &x, double &y) {
+        const unsigned long long ux = (unsigned long long)__double_as_longlong(x);
+        const unsigned long long uy = (unsigned long long)__double_as_longlong(y);
+        unsigned x2[2] = {(unsigned)ux, (unsigned)(ux >> 32)}, y2[2] = {(unsigned)uy, (unsigned)(uy >> 32)};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if constexpr (SWAP == 32) {
+                const auto r = __builtin_amdgcn_permlane32_swap(x2[k], y2[k], false, false);
+                x2[k] = r[0];
+                y2[k] = r[1];
+            } else {
+                const auto r = __builtin_amdgcn_permlane16_swap(x2[k], y2[k], false, false);
+                x2[k] = r[0];
+                y2[k] = r[1];
+            }
+        }
+        x = __longlong_as_double((long long)(((unsigned long long)x2[1] << 32) | x2[0]));
+        y = __longlong_as_double((long long)(((unsigned long long)y2[1] << 32) | y2[0]));
+    };
+    one(a.hi, b.hi);
+    one(a.lo, b.lo);
+}
+
+// Sums of eight double-doubles over the 64 lanes: lane l returns the sum of
+// v[l / 8].  Each exchange leaves a lane half as many values, so it takes 10
+// additions where eight wave_sums take 48.
+__device__ __forceinline__ dd wave_sum8(dd (&v)[8], int lane)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // lanes 32-63 take v[k + 4]
+        dd_swap<32>(v[k], v[k + 4]);
+        v[k] = dd_add(v[k], v[k + 4]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {  // odd rows take v[k + 2]
+        dd_swap<16>(v[k], v[k + 2]);
+        v[k] = dd_add(v[k], v[k + 2]);
+    }
+    const bool up = lane & 8;  // the upper half of a row takes v[1]
+    const dd keep = up ? v[1] : v[0], give = up ? v[0] : v[1];
+    dd s = dd_add(keep, dd{dpp_double<0x128, 0xf>(give.hi), dpp_double<0x128, 0xf>(give.lo)});  // row_ror:8
+    s = dd_add_dpp<0x141, 0xf>(s);  // row_half_mirror
+    s = dd_add_dpp<0x4e, 0xf>(s);   // quad_perm [2, 3, 0, 1]
+    return dd_add_dpp<0xb1, 0xf>(s);  // quad_perm [1, 0, 3, 2]
+}
+
 // Sum of a double-double over lanes 0 .. width-1 (width a power of two, at
 // most 64; the other lanes' values are ignored): an xor butterfly, so every
 // lane of a group of `width` ends with the same sum after log2(width)
