@@ -14,7 +14,8 @@
 //    memory (the same workgroup writes and reads them between barriers).
 //  - Teams (optional): `team` resident workgroups solve one system
 //    together, each a contiguous chunk of its rows, and meet at team
-//    barriers and all-reduces through device memory.  Teams claim from the
+//    barriers and all-reduces through device memory; a member's rows of p are
+//    in its LDS too, where they fit.  Teams claim from the
 //    large end of the order and single workgroups from the small end, so
 //    the two meet where their work balances.  The arithmetic is that of the single-system mixed
 // method (FK_CG_MIXED): rows summed left to right, inner products of exact
@@ -52,6 +53,8 @@ struct BatchArgs {
     const int32_t *row_ptr, *col_idx;
     const double *vals;
     const float *vals32;
+    const int32_t *sl_ptr;  // [n / 64] sliced copy of the matrix (null: none)
+    const int2 *sl;         // its entries: {column within the system, FP32 value}
     const double *b;
     double *x;
     float *r32, *p32, *ap32, *d32;  // device work vectors, indexed by global row
@@ -113,7 +116,7 @@ struct Team {
 // T members have.  The wait is bounded: after spin_limit polls, or when
 // another wait has already given up, it sets the abort flag and returns
 // false.  The caller's stores must be complete (s_waitcnt) before it.
-__device__ bool team_arrive_wait(const BatchArgs &a, const Team &tm)
+__device__ __forceinline__ bool team_arrive_wait(const BatchArgs &a, const Team &tm)
 {
     uint32_t *cnt = a.team_cnt + (size_t)tm.t * CNT_STRIDE;
     __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -137,7 +140,7 @@ __device__ __forceinline__ double *team_slot(const BatchArgs &a, const Team &tm,
 
 // Team barrier: every member's earlier stores are visible to every member
 // after it.  false if the team gave up.
-__device__ bool team_barrier(const BatchArgs &a, Team &tm, double *bcast)
+__device__ __forceinline__ bool team_barrier(const BatchArgs &a, Team &tm, double *bcast)
 {
     __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have completed
     __syncthreads();
@@ -159,7 +162,7 @@ __device__ bool team_barrier(const BatchArgs &a, Team &tm, double *bcast)
 // lane 0 publishes and waits in between.  It is also a team barrier.
 // false if the team gave up.
 template <int K, int NW>
-__device__ bool team_reduce(const BatchArgs &a, Team &tm, dd (&v)[K], double (&out)[K], dd (*lds)[NW],
+__device__ __forceinline__ bool team_reduce(const BatchArgs &a, Team &tm, dd (&v)[K], double (&out)[K], dd (*lds)[NW],
                             double *bcast)
 {
     static_assert(K < 4 && K <= KMAX, "broadcast words");
@@ -284,79 +287,124 @@ __device__ __forceinline__ T row_sum(const int32_t *__restrict__ col, const T *_
     return q;
 }
 
-// Two rows summed left to right at once (each in its own order, as
-// row_sum): up to RB2 indices and values of each, then their gathers, are
-// requested together, so a thread has more loads in flight.  (With 1024
-// threads this spills a few registers; measured, the wider requests still
-// win: 868 -> 704 us per inner iteration of a 512^2 system alone.)
-constexpr int RB2 = 6;
-template <typename T, typename V, bool COH>
-__device__ __forceinline__ void row_sum2(const int32_t *__restrict__ col, const T *__restrict__ vals,
-                                         const V *__restrict__ x, int a0, int a1, int b0, int b1, int shift,
-                                         T &qa, T &qb)
+// The inner solve's p as a workgroup sees it.  own(i) is one of its rows,
+// at(c) any row of the system.
+struct PlainP {  // the workgroup's alone (LDS or device memory)
+    float *p;
+    __device__ __forceinline__ float own(int i) const { return p[i]; }
+    __device__ __forceinline__ float at(int c) const { return p[c]; }
+    __device__ __forceinline__ void put(int i, float v) const { p[i] = v; }
+};
+
+struct TeamP {  // shared by a team, in device memory
+    float *p;
+    __device__ __forceinline__ float own(int i) const { return ld_coh(p + i); }
+    __device__ __forceinline__ float at(int c) const { return ld_coh(p + c); }
+    __device__ __forceinline__ void put(int i, float v) const { st_coh(p + i, v); }
+};
+
+// Shared by a team, with the member's rows [lo, lo + cnt) in its LDS as well:
+// only the rows of other members are read through the coherent path, which
+// no cache near the workgroup serves.  With the sliced copy below: 128 systems
+// of 16^2 to 512^2 in 30.2 ms, 40.9 with every gather coherent and the matrix
+// in CSR.  What is left is mostly the two meetings of an iteration (teams of 8
+// took 32.3 ms, of 32 47.2 ms).
+struct TeamOwnP {
+    float *p, *mine;
+    int lo;
+    unsigned cnt;
+    __device__ __forceinline__ float own(int i) const { return mine[i - lo]; }
+    __device__ __forceinline__ float at(int c) const
+    {
+        const unsigned u = (unsigned)(c - lo);
+        return u < cnt ? mine[u] : ld_coh(p + c);
+    }
+    __device__ __forceinline__ void put(int i, float v) const
+    {
+        mine[i - lo] = v;
+        st_coh(p + i, v);
+    }
+};
+
+// Where the entries of a row lie: row r0 + i of the CSR arrays, or of their
+// sliced copy (slices of 64 rows, entry k of a slice's rows side by side, so
+// the 64 lanes of a wave read 512 contiguous bytes where CSR has them read
+// 4 bytes in every row's stretch).
+struct CsrRow {
+    const int32_t *col;
+    const float *val;
+    int shift;
+    __device__ __forceinline__ int2 operator()(int k) const { return int2{col[k] - shift, __float_as_int(val[k])}; }
+};
+
+struct SlicedRow {
+    const int2 *e;
+    __device__ __forceinline__ int2 operator()(int k) const { return e[(size_t)k * SLICE]; }
+};
+
+template <bool SL>
+__device__ __forceinline__ auto row_entries(const BatchArgs &a, int r0, int i, int &len)
 {
-    qa = T(0);
-    qb = T(0);
-    const int la = a1 - a0, lb = b1 - b0;
+    const int g = r0 + i, j0 = a.row_ptr[g];
+    len = a.row_ptr[g + 1] - j0;
+    if constexpr (SL)
+        return SlicedRow{a.sl + a.sl_ptr[g / SLICE] + g % SLICE};
+    else
+        return CsrRow{a.col_idx + j0, a.vals32 + j0, r0};
+}
+
+// Two rows summed left to right at once (each in its own order, as
+// row_sum): up to RB2 entries of each, then their gathers, are requested
+// together, so a thread has more loads in flight (868 -> 704 us per inner
+// iteration of a 512^2 system alone, against one row at a time).  128 systems
+// of 16^2 to 512^2 took 31.5 ms with 4 entries, 30.2 with 5, 34.7 with 6 and
+// 38.7 with 8: from 6 on, 1024 threads spill 119 registers and more.
+constexpr int RB2 = 5;
+template <typename ROW, typename VEC>
+__device__ __forceinline__ void row_sum2(const ROW &rowa, const ROW &rowb, int la, int lb, const VEC &P, float &qa,
+                                         float &qb)
+{
+    qa = 0.f;
+    qb = 0.f;
     const int len = la > lb ? la : lb;
     for (int j = 0; j < len; j += RB2) {
-        int ca[RB2], cb[RB2];
-        T va[RB2], vb[RB2];
-#pragma unroll
-        for (int k = 0; k < RB2; ++k) {
-            if (j + k < la) {
-                ca[k] = col[a0 + j + k] - shift;
-                va[k] = vals[a0 + j + k];
-            }
-            if (j + k < lb) {
-                cb[k] = col[b0 + j + k] - shift;
-                vb[k] = vals[b0 + j + k];
-            }
-        }
-        T ga[RB2], gb[RB2];
+        int2 ea[RB2], eb[RB2];
 #pragma unroll
         for (int k = 0; k < RB2; ++k) {
             if (j + k < la)
-                ga[k] = (T)(COH ? ld_coh(x + ca[k]) : x[ca[k]]);
+                ea[k] = rowa(j + k);
             if (j + k < lb)
-                gb[k] = (T)(COH ? ld_coh(x + cb[k]) : x[cb[k]]);
+                eb[k] = rowb(j + k);
+        }
+        float ga[RB2], gb[RB2];
+#pragma unroll
+        for (int k = 0; k < RB2; ++k) {
+            if (j + k < la)
+                ga[k] = P.at(ea[k].x);
+            if (j + k < lb)
+                gb[k] = P.at(eb[k].x);
         }
 #pragma unroll
         for (int k = 0; k < RB2; ++k) {
             if (j + k < la)
-                qa = qa + va[k] * ga[k];
+                qa = qa + __int_as_float(ea[k].y) * ga[k];
             if (j + k < lb)
-                qb = qb + vb[k] * gb[k];
+                qb = qb + __int_as_float(eb[k].y) * gb[k];
         }
     }
 }
 
-template <bool COH>
-__device__ __forceinline__ float ldp(const float *p)
-{
-    return COH ? ld_coh(p) : *p;
-}
-
-template <bool COH>
-__device__ __forceinline__ void stp(float *p, float v)
-{
-    if constexpr (COH)
-        st_coh(p, v);
-    else
-        *p = v;
-}
-
 // The inner update d += alpha p, r -= alpha Ap, p = r + beta p over one
 // thread's rows i0, i0 + WGS, ... < i1, two rows per step with their loads
-// together; <r,r> accumulates in row order.  COH: p is shared by a team.
-template <int WGS, bool COH>
-__device__ __forceinline__ void inner_update(float *R, float *P, const float *AP, float *D, int i0, int i1,
+// together; <r,r> accumulates in row order.
+template <int WGS, typename VEC>
+__device__ __forceinline__ void inner_update(float *R, const VEC &P, const float *AP, float *D, int i0, int i1,
                                              float af, float bf, dd &rr)
 {
     int i = i0;
     for (; i + WGS < i1; i += 2 * WGS) {
         const int i2 = i + WGS;
-        const float pa = ldp<COH>(P + i), pb = ldp<COH>(P + i2);
+        const float pa = P.own(i), pb = P.own(i2);
         const float da = D[i], db = D[i2];
         const float ra = R[i], rb = R[i2];
         const float ya = AP[i], yb = AP[i2];
@@ -365,47 +413,56 @@ __device__ __forceinline__ void inner_update(float *R, float *P, const float *AP
         const float sa = ra - af * ya, sb = rb - af * yb;
         R[i] = sa;
         R[i2] = sb;
-        stp<COH>(P + i, sa + bf * pa);
-        stp<COH>(P + i2, sb + bf * pb);
+        P.put(i, sa + bf * pa);
+        P.put(i2, sb + bf * pb);
         dd_fma(rr, (double)sa, (double)sa);
         dd_fma(rr, (double)sb, (double)sb);
     }
     if (i < i1) {
-        const float pi = ldp<COH>(P + i);
+        const float pi = P.own(i);
         D[i] = D[i] + af * pi;
         const float ri = R[i] - af * AP[i];
         R[i] = ri;
-        stp<COH>(P + i, ri + bf * pi);
+        P.put(i, ri + bf * pi);
         dd_fma(rr, (double)ri, (double)ri);
     }
 }
 
 // The inner product Ap over one thread's rows (two per step, as above) with
 // <p,Ap> and <Ap,Ap> accumulated in row order.
-template <int WGS, bool COH>
-__device__ __forceinline__ void inner_product(const BatchArgs &a, int r0, const float *P, float *AP, int i0,
-                                              int i1, dd &pap, dd &apap)
+template <int WGS, bool SL, typename VEC>
+__device__ __forceinline__ void inner_product_of(const BatchArgs &a, int r0, const VEC &P, float *AP, int i0, int i1,
+                                                 dd &pap, dd &apap)
 {
     int i = i0;
-    for (; i + WGS < i1; i += 2 * WGS) {
+    for (; i < i1; i += 2 * WGS) {
         const int i2 = i + WGS;
+        int la, lb = 0;
+        const auto rowa = row_entries<SL>(a, r0, i, la);
+        auto rowb = rowa;
+        if (i2 < i1)
+            rowb = row_entries<SL>(a, r0, i2, lb);
         float qa, qb;
-        row_sum2<float, float, COH>(a.col_idx, a.vals32, P, a.row_ptr[r0 + i], a.row_ptr[r0 + i + 1],
-                                    a.row_ptr[r0 + i2], a.row_ptr[r0 + i2 + 1], r0, qa, qb);
+        row_sum2(rowa, rowb, la, lb, P, qa, qb);
         AP[i] = qa;
-        AP[i2] = qb;
-        dd_fma(pap, (double)qa, (double)ldp<COH>(P + i));
+        dd_fma(pap, (double)qa, (double)P.own(i));
         dd_fma(apap, (double)qa, (double)qa);
-        dd_fma(pap, (double)qb, (double)ldp<COH>(P + i2));
-        dd_fma(apap, (double)qb, (double)qb);
+        if (i2 < i1) {
+            AP[i2] = qb;
+            dd_fma(pap, (double)qb, (double)P.own(i2));
+            dd_fma(apap, (double)qb, (double)qb);
+        }
     }
-    if (i < i1) {
-        const float q = row_sum<float, float, COH>(a.col_idx, a.vals32, P, a.row_ptr[r0 + i],
-                                                   a.row_ptr[r0 + i + 1], r0);
-        AP[i] = q;
-        dd_fma(pap, (double)q, (double)ldp<COH>(P + i));
-        dd_fma(apap, (double)q, (double)q);
-    }
+}
+
+template <int WGS, typename VEC>
+__device__ __forceinline__ void inner_product(const BatchArgs &a, int r0, const VEC &P, float *AP, int i0, int i1,
+                                              dd &pap, dd &apap)
+{
+    if (a.sl_ptr)
+        inner_product_of<WGS, true>(a, r0, P, AP, i0, i1, pap, apap);
+    else
+        inner_product_of<WGS, false>(a, r0, P, AP, i0, i1, pap, apap);
 }
 
 // One system of the batch, solved by the whole workgroup.  IN_LDS: its four
@@ -422,7 +479,7 @@ __device__ __forceinline__ void solve_one(const BatchArgs &a, int s, float *vlds
     // IN_LDS is a compile-time choice, so each vector has one address
     // space and compiles to ds_* or global_* accesses (not flat).
     float *R = IN_LDS ? vlds : a.r32 + r0;
-    float *P = IN_LDS ? vlds + a.lds_rows : a.p32 + r0;
+    const PlainP P{IN_LDS ? vlds + a.lds_rows : a.p32 + r0};
     float *AP = IN_LDS ? vlds + 2 * a.lds_rows : a.ap32 + r0;
     float *D = IN_LDS ? vlds + 3 * a.lds_rows : a.d32 + r0;
     const int64_t max_iter = a.max_iter > 0 ? a.max_iter : 10 * (int64_t)n;
@@ -473,7 +530,7 @@ __device__ __forceinline__ void solve_one(const BatchArgs &a, int s, float *vlds
         dd ai[1] = {dd{0.0, 0.0}};
         for (int i = tid; i < n; i += WGS) {
             const float ri = R[i];
-            P[i] = ri;
+            P.put(i, ri);
             D[i] = 0.f;
             dd_fma(ai[0], (double)ri, (double)ri);
         }
@@ -494,10 +551,10 @@ __device__ __forceinline__ void solve_one(const BatchArgs &a, int s, float *vlds
                 // it == 0: product only; it >= 1: update, then product.
                 dd acc3[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
                 if (!first) {
-                    inner_update<WGS, false>(R, P, AP, D, tid, n, (float)alpha, (float)beta, acc3[0]);
+                    inner_update<WGS>(R, P, AP, D, tid, n, (float)alpha, (float)beta, acc3[0]);
                     __syncthreads();  // p complete before the product
                 }
-                inner_product<WGS, false>(a, r0, P, AP, tid, n, acc3[1], acc3[2]);
+                inner_product<WGS>(a, r0, P, AP, tid, n, acc3[1], acc3[2]);
                 double d3[3];
                 wg_reduce<3, NW>(acc3, d3, red, bcast);
                 if (!first) {
@@ -554,8 +611,9 @@ __device__ __forceinline__ void solve_one(const BatchArgs &a, int s, float *vlds
 // the member that owns the row.  Every member takes every decision on the
 // same reduced values, so all meet the same number of times.  false: the
 // team gave up waiting (the system keeps status B_UNSOLVED).
-template <int WGS>
-__device__ bool solve_team(const BatchArgs &a, int s, Team &tm, dd (*red)[WGS / 64], double *bcast)
+template <int WGS, bool OWN_LDS>
+__device__ __forceinline__ bool solve_team(const BatchArgs &a, int s, Team &tm, float *vlds, dd (*red)[WGS / 64],
+                                           double *bcast)
 {
     constexpr int NW = WGS / 64;
     const int tid = threadIdx.x;
@@ -563,7 +621,13 @@ __device__ bool solve_team(const BatchArgs &a, int s, Team &tm, dd (*red)[WGS / 
     const int n = a.sys_ptr[s + 1] - r0;
     const int chunk = (n + tm.T - 1) / tm.T;
     const int lo = min(n, tm.j * chunk), hi = min(n, lo + chunk);
-    float *R = a.r32 + r0, *P = a.p32 + r0, *AP = a.ap32 + r0, *D = a.d32 + r0;
+    float *R = a.r32 + r0, *AP = a.ap32 + r0, *D = a.d32 + r0;
+    const auto P = [&] {
+        if constexpr (OWN_LDS)
+            return TeamOwnP{a.p32 + r0, vlds, lo, (unsigned)(hi - lo)};
+        else
+            return TeamP{a.p32 + r0};
+    }();
     double *X = a.x + r0;
     const int64_t max_iter = a.max_iter > 0 ? a.max_iter : 10 * (int64_t)n;
     int64_t used = 0;
@@ -614,7 +678,7 @@ __device__ bool solve_team(const BatchArgs &a, int s, Team &tm, dd (*red)[WGS / 
         dd ai[1] = {dd{0.0, 0.0}};
         for (int i = lo + tid; i < hi; i += WGS) {
             const float ri = R[i];
-            st_coh(P + i, ri);
+            P.put(i, ri);
             D[i] = 0.f;
             dd_fma(ai[0], (double)ri, (double)ri);
         }
@@ -636,11 +700,11 @@ __device__ bool solve_team(const BatchArgs &a, int s, Team &tm, dd (*red)[WGS / 
                 // it == 0: product only; it >= 1: update, then product.
                 dd acc3[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
                 if (!first) {
-                    inner_update<WGS, true>(R, P, AP, D, lo + tid, hi, (float)alpha, (float)beta, acc3[0]);
+                    inner_update<WGS>(R, P, AP, D, lo + tid, hi, (float)alpha, (float)beta, acc3[0]);
                     if (!team_barrier(a, tm, bcast))  // p complete before the product
                         return false;
                 }
-                inner_product<WGS, true>(a, r0, P, AP, lo + tid, hi, acc3[1], acc3[2]);
+                inner_product<WGS>(a, r0, P, AP, lo + tid, hi, acc3[1], acc3[2]);
                 double d3[3];
                 if (!team_reduce<3, NW>(a, tm, acc3, d3, red, bcast))
                     return false;
@@ -696,8 +760,8 @@ __device__ bool solve_team(const BatchArgs &a, int s, Team &tm, dd (*red)[WGS / 
 // it fits), claim again.  `first`, if not negative, is a system already
 // claimed.
 template <int WGS>
-__device__ void single_loop(const BatchArgs &a, bool front, int first, float *vlds, dd (*red)[WGS / 64],
-                            double *bcast, int32_t *s_sys)
+__device__ __forceinline__ void single_loop(const BatchArgs &a, bool front, int first, float *vlds,
+                                            dd (*red)[WGS / 64], double *bcast, int32_t *s_sys)
 {
     for (int s = first;;) {
         if (s < 0) {
@@ -725,7 +789,7 @@ __device__ void single_loop(const BatchArgs &a, bool front, int first, float *vl
 // it is larger: the team then dissolves, its first member solves that
 // system alone and every member goes on as a single workgroup.
 template <int WGS>
-__device__ void team_loop(const BatchArgs &a, Team tm, float *vlds, dd (*red)[WGS / 64], double *bcast,
+__device__ __forceinline__ void team_loop(const BatchArgs &a, Team tm, float *vlds, dd (*red)[WGS / 64], double *bcast,
                           int32_t *s_sys)
 {
     for (;;) {
@@ -744,7 +808,13 @@ __device__ void team_loop(const BatchArgs &a, Team tm, float *vlds, dd (*red)[WG
             single_loop<WGS>(a, true, tm.j == 0 ? s : -1, vlds, red, bcast, s_sys);
             return;
         }
-        if (!solve_team<WGS>(a, s, tm, red, bcast))
+        // A member's rows of p in its LDS (which the four vectors of a small
+        // system would fill) where they fit.
+        const int n = a.sys_ptr[s + 1] - a.sys_ptr[s];
+        const bool done = (n + tm.T - 1) / tm.T <= 4 * a.lds_rows
+                              ? solve_team<WGS, true>(a, s, tm, vlds, red, bcast)
+                              : solve_team<WGS, false>(a, s, tm, vlds, red, bcast);
+        if (!done)
             return;
     }
 }
@@ -788,6 +858,28 @@ __global__ __launch_bounds__(256) void k_to_f32_batch(int64_t n, float *out, con
         out[i] = (float)in[i];
 }
 
+// The sliced copy: row g's entries to sl_ptr[g / 64] + k 64 + g % 64, columns
+// counted from the first row of its system.
+__global__ __launch_bounds__(256) void k_slice_batch(int64_t n, int32_t count, const int32_t *sys_ptr,
+                                                     const int32_t *row_ptr, const int32_t *col_idx,
+                                                     const double *vals, const int32_t *sl_ptr, int2 *sl)
+{
+    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < n; g += (int64_t)gridDim.x * 256) {
+        int lo = 0, hi = count;  // sys_ptr[lo] <= g < sys_ptr[hi]
+        while (hi - lo > 1) {
+            const int mid = lo + (hi - lo) / 2;
+            if (sys_ptr[mid] <= g)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        const int r0 = sys_ptr[lo], j0 = row_ptr[g], len = row_ptr[g + 1] - j0;
+        int2 *e = sl + sl_ptr[g / SLICE] + g % SLICE;
+        for (int k = 0; k < len; ++k)
+            e[(size_t)k * SLICE] = int2{col_idx[j0 + k] - r0, __float_as_int((float)vals[j0 + k])};
+    }
+}
+
 }  // namespace batch
 }  // namespace fk
 
@@ -807,6 +899,8 @@ struct fk_batch_s {
     int32_t *status = nullptr, *iters = nullptr, *sweeps = nullptr;
     double *rel = nullptr;
     int32_t max_rows = 0;
+    int32_t *sl_ptr = nullptr;  // sliced copy of the matrix (null: none)
+    int2 *sl = nullptr;
     // team scratch, grown on demand: counters, partial slots, announced
     // systems for up to team_cap_n teams of up to team_cap_t members
     uint32_t *team_cnt = nullptr;
@@ -847,6 +941,8 @@ void release(fk_batch B)
     dfree(B->col_idx);
     dfree(B->vals);
     dfree(B->vals32);
+    dfree(B->sl_ptr);
+    dfree(B->sl);
     dfree(B->r32);
     dfree(B->p32);
     dfree(B->ap32);
@@ -957,6 +1053,25 @@ extern "C" fk_status fk_batch_create(int32_t count, const int64_t *sys_ptr, int6
         }
         sys_nnz[(size_t)s] = rp[hi] - rp[lo];
     }
+    // Slices of the matrix's sliced copy, as wide as their longest row.  Where
+    // that is more than twice the nonzeros (one long row among short ones) or
+    // past 32 bits, there is no copy and the solves read the CSR arrays.
+    std::vector<int32_t> sl_ptr;
+    int64_t sl_len = 0;
+    try {
+        sl_ptr.reserve((size_t)((n + SLICE - 1) / SLICE));
+    } catch (const std::bad_alloc &) {
+        return internal_fail(FK_E_OOM, "host allocation failed");
+    }
+    for (int64_t g = 0; g < n; g += SLICE) {
+        int32_t width = 0;
+        for (int64_t i = g; i < std::min<int64_t>(n, g + SLICE); ++i)
+            width = std::max(width, rp[i + 1] - rp[i]);
+        if (sl_len <= INT32_MAX)
+            sl_ptr.push_back((int32_t)sl_len);
+        sl_len += (int64_t)width * SLICE;
+    }
+    const bool sliced = sl_len <= INT32_MAX && sl_len <= 2 * nnz + 64 * SLICE;
     // Largest systems first (ties by index), so the longest solves start early.
     std::vector<int32_t> order((size_t)count);
     std::iota(order.begin(), order.end(), 0);
@@ -1000,6 +1115,18 @@ extern "C" fk_status fk_batch_create(int32_t count, const int64_t *sys_ptr, int6
     }
     if (e == hipSuccess && nnz > 0)
         hipLaunchKernelGGL(k_to_f32_batch, dim3(2048), dim3(256), 0, st, nnz, B->vals32, B->vals);
+    if (e == hipSuccess && sliced && nnz > 0) {
+        if (dalloc(&B->sl_ptr, sl_ptr.size()) == hipSuccess && dalloc(&B->sl, (size_t)sl_len) == hipSuccess) {
+            e = hipMemcpyAsync(B->sl_ptr, sl_ptr.data(), sl_ptr.size() * 4, hipMemcpyHostToDevice, st);
+            if (e == hipSuccess)
+                hipLaunchKernelGGL(k_slice_batch, dim3(2048), dim3(256), 0, st, n, count, B->sys_ptr, B->row_ptr,
+                                   B->col_idx, B->vals, B->sl_ptr, B->sl);
+        } else {  // no memory for the copy: the solves do without
+            (void)hipGetLastError();
+            dfree(B->sl_ptr);
+            dfree(B->sl);
+        }
+    }
     e = e ? e : hipGetLastError();
     e = e ? e : hipStreamSynchronize(st);
     if (e != hipSuccess) {
@@ -1060,6 +1187,8 @@ extern "C" fk_status fk_batch_solve(fk_batch B, const fk_batch_opts *o, const do
     a.col_idx = B->col_idx;
     a.vals = B->vals;
     a.vals32 = B->vals32;
+    a.sl_ptr = B->sl_ptr;
+    a.sl = B->sl;
     a.b = b;
     a.x = x;
     a.r32 = B->r32;

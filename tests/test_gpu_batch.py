@@ -177,3 +177,36 @@ def test_batch_config_full(team, device):
     print(f"[result] inner iterations per system: min {res.iterations.min()} median "
           f"{int(np.median(res.iterations))} max {res.iterations.max()}; sweeps max {res.sweeps.max()}",
           flush=True)
+
+
+def _band(n, half):
+    """Diagonally dominant band matrix: rows of up to 2 half + 1 entries."""
+    i = np.arange(n)
+    M = -(np.abs(i[:, None] - i[None, :]) <= half).astype(float)
+    M[i, i] = 2 * half + 1.5 + 0.5 * np.cos(i)
+    return M
+
+
+@pytest.mark.parametrize("team", [1, 3, 8])
+@pytest.mark.parametrize("long_row", [False, True], ids=["sliced", "csr"])
+def test_batch_row_storage(long_row, team, device):
+    """Rows at the edges of the entries read at once (lengths 1, 3, 5, 7 and
+    11, fewer at the ends) in systems that end inside, at and past a slice of
+    64 rows; with one long row among them, which the sliced copy leaves to the
+    CSR arrays.  With 100 rows of LDS the two large systems are solved by
+    teams whose members keep their rows of p in LDS (teams of 8) or read them
+    all from device memory (teams of 3, 500 rows each)."""
+    mats = [P.dense_to_csr(_band(n, h)) for n, h in ((63, 0), (64, 1), (65, 2), (1500, 3), (700, 5))]
+    if long_row:
+        M = _band(1500, 1)
+        M[0, 1:] = M[1:, 0] = -1e-3
+        mats.append(P.dense_to_csr(M))
+    A, sp = P.block_diagonal(mats)
+    b = np.random.default_rng(11).uniform(-1, 1, A.n)
+    refs = oracle_batch(A, sp, b, rtol=1e-10, inner_rtol=1e-4)
+    B = fk.Batch(A, sp)
+    for lds_rows in (0, 100, -1):
+        print(f"\n[case] storage long_row={long_row} team={team} lds_rows={lds_rows}", flush=True)
+        xd = dev(np.zeros(A.n))
+        B.solve(dev(b), xd, rtol=1e-10, inner_rtol=1e-4, team=team, lds_rows=lds_rows)
+        assert_batch_equal(B, host(xd), refs, sp, f"lds{lds_rows}")
