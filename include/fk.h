@@ -252,7 +252,7 @@ fk_status fk_csr_stream(fk_csr A, int32_t *streaming, int32_t *sweep);
  * iterates equal those of the multi-kernel path; FK_FLAG_NO_SMALL disables
  * that.  fk_solver_uses_small() tells which path a solver takes.
  *
- * Pipelined CG and BiCGStab solves of larger systems (n >= 4096) whose matrix
+ * Pipelined CG and BiCGStab solves of larger systems (n >= 2048) whose matrix
  * is in a sliced layout of at most seven entries per row and whose vectors fit
  * the registers and LDS of the chip (beyond about a million unknowns CG alone,
  * up to two million, reading the matrix from the caches) run as one launch of

@@ -1084,14 +1084,17 @@ static std::atomic<int> &resident_units(int device)
 constexpr int RES_CHUNK = 8192;
 constexpr uint32_t RES_TAGS = 2 * RES_CHUNK + 8;  // tags a launch may use: two products an iteration
 // Fewest unknowns of a solve on several resident workgroups; below, one
-// workgroup solves alone.  us per iteration, resident / launch per step:
-// 2D Poisson CG 3.5 / 11.6 at n = 16,129, 5.3 / 15.6 at 261,121, 9.3 / 29.7
+// workgroup solves alone (BiCGStab up to 2048 unknowns, the one-kernel CG up
+// to 3072, CG up to 4096), or the caller asked for the multi-kernel path.  us
+// per iteration, resident / launch per step: 2D Poisson CG 3.4 / 9.7 (one
+// kernel) at n = 3,969, 3.5 / 11.6 at 16,129, 5.3 / 15.6 at 261,121, 9.3 / 29.7
 // at 1,000,000; 3D 5.8 / 17.0 at 262,144, 8.9 / 23.4 at 512,000, 37.3 / 50.8 at
-// 2,097,152 (matrix streamed); BiCGStab on 2D convection-diffusion 7.0 / 18.8
-// at 4,096, 11.3 / 26.0 at 261,121, 28.6 / 53 at 1,048,576.  One workgroup, these kernels / the CSR kernels of
+// 2,097,152 (matrix streamed); BiCGStab on 2D convection-diffusion 7.1 / 19.6
+// at 2,116, 7.1 / 19.3 at 3,969, 11.3 / 26.0 at 261,121, 28.6 / 53 at
+// 1,048,576.  One workgroup, these kernels / the CSR kernels of
 // fk_kernels.hip: CG 2.0 / 3.5 at n = 1,024, 4.4 / 10.1 at 3,969; BiCGStab
 // 4.2 / 8.0 at 1,024.
-constexpr int64_t RES_MIN_N = 4096;
+constexpr int64_t RES_MIN_N = 2048;
 
 // Which solves are resident: the pipelined methods on a sliced layout of at
 // most seven entries per row whose rows, with their ghosts, fit the chip (the

@@ -61,6 +61,14 @@ def test_rows_one_workgroup(nx, ny, device):
         _check(P.heat2d(nx, ny=ny), its, method="bicgstab_pipelined_2k")
 
 
+# sizes past the single workgroup's (2048 for BiCGStab, 3072 for the one-kernel
+# CG) and below and at 16 whole workgroups
+@pytest.mark.parametrize("nx,ny", [(683, 3), (439, 7), (63, 65), (64, 64)])
+def test_rows_few_workgroups(nx, ny, device):
+    _check(P.heat2d(nx, ny=ny), 6, method="bicgstab_pipelined_2k")
+    _check(P.heat2d(nx, ny=ny), 6, method="cg_pipelined_1k")
+
+
 @pytest.mark.parametrize("n", [7, 12, 16])
 def test_rows_one_workgroup_3d(n, device):
     _check(P.poisson3d(n), 6)
