@@ -901,8 +901,10 @@ def main():
                      "bytes_per_launch": spmv_layout_b, "avg_us": spmv_us,
                      "csr_bytes_per_launch": spmv_b, "csr_achieved": achieved,
                      "csr_frac": achieved / PEAK_HBM_GBS,
-                     "note": "128^3's working set fits the 256 MB Infinity Cache; extra.poisson3d_192_* "
-                             "is the point beyond it",
+                     "note": "kernel times are of a profiled solve, which runs launch per step; the timed "
+                             "solves run resident, in one launch, and move fewer bytes than extra.iteration_* "
+                             "counts. 128^3's working set fits the 256 MB Infinity Cache; "
+                             "extra.poisson3d_192_* is the point beyond it",
                      "update_dot_avg_us": upd_us},
         "cpu_baseline": cpu,
         "extra": extras,
