@@ -518,7 +518,10 @@ fk_status fk_net_train_step(fk_net N, fk_csr A, int32_t nx, int32_t ny, const do
  * captured once into a hipGraph and replayed while the arguments stay the
  * same.  The call waits for completion.  Per system: converged when
  * ||b_s - A_s x_s|| <= rtol ||b_s||; max_iter counts inner iterations over
- * all sweeps (0 = 10 n_s); b_s = 0 gives x_s = 0.
+ * all sweeps (0 = 10 n_s); b_s = 0 gives x_s = 0.  fk_batch_create keeps the
+ * matrix twice, as CSR and (8 bytes per stored entry) in slices of 64 rows, the
+ * latter unless rows of very uneven length would pad it past twice the
+ * nonzeros or device memory runs short.
  */
 typedef struct {
     double rtol;        /* >= 0                                              */
