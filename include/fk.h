@@ -383,6 +383,15 @@ fk_status fk_get_refinements(fk_solver S, int32_t *sweeps);
 fk_status fk_spmv(fk_csr A, const double *p_dev, double *q_dev, double *dots_host, void *hip_stream);
 
 /*
+ * For tests of the error path: in the next fk_spmv with dots on A, the leader
+ * of workgroups 64 group .. 64 group + 63 of the reduction reports that it ran
+ * out of polls, as if a member's partial sums had not arrived.  That call then
+ * returns FK_E_HIP (when the product has such a group); later ones are whole.
+ * FK_E_ARG for a group outside [0, 64).
+ */
+fk_status fk_csr_test_fault(fk_csr A, int32_t group);
+
+/*
  * The kernel time of q = A p (Section 2.2's product): `reps` launches back
  * to back, each carrying two HIP events that the device stamps when the
  * kernel itself starts and ends; *avg_us receives their average duration.

@@ -153,8 +153,9 @@ struct fk_csr_s {
     int64_t stride1 = 0, stride2 = 0;  // slots: the largest offset (2), the largest at most half of it (1)
     int32_t layout = FK_LAYOUT_ROW_BLOCKS;  // layout the products read
     // scratch reduction state for fk_spmv / fk_spmv32, and pinned memory that
-    // takes fk_spmv's dots, then 1.0
+    // takes fk_spmv's dots (RedArgs::host)
     double *h_dots = nullptr;
+    int32_t test_fault = 0;  // 1 + the group of fk_csr_test_fault
     DevState *st = nullptr;
     double *partials = nullptr;
     int solvers = 0;
@@ -670,7 +671,7 @@ extern "C" fk_status fk_csr_create(int64_t n, int64_t nnz, const int32_t *row_pt
     CSR_TRY(dev_alloc(&A->block_j0, blocks.size(), "row blocks"));
     CSR_TRY(dev_alloc(&A->st, 1, "state"));
     CSR_TRY(dev_alloc(&A->partials, RED_SCRATCH_DOUBLES, "partials"));
-    CSR_HIP(hipHostMalloc(reinterpret_cast<void **>(&A->h_dots), (KMAX + 1) * sizeof(double), hipHostMallocDefault));
+    CSR_HIP(hipHostMalloc(reinterpret_cast<void **>(&A->h_dots), HOST_WORDS * sizeof(double), hipHostMallocDefault));
     CSR_HIP(hipMemcpyAsync(A->row_ptr, row_ptr, (size_t)(n + 1) * 4, kind, s));
     if (nnz > 0) {
         CSR_HIP(hipMemcpyAsync(A->col_idx, col_idx, (size_t)nnz * 4, kind, s));
@@ -2356,18 +2357,31 @@ extern "C" fk_status fk_spmv(fk_csr A, const double *p, double *q, double *dots_
         // The reduction leaves the dots in pinned memory; copying the state to
         // the caller's stack after it cost a third of a small call (20,011
         // rows: 33 us, 25 without).
-        A->h_dots[KMAX] = 0.0;
+        A->h_dots[HOST_DONE] = 0.0;
+        A->h_dots[HOST_FAULT] = 0.0;
         red.host = A->h_dots;
+        red.npub = A->test_fault;
+        A->test_fault = 0;
     }
     HIP_TRY(launch_spmv_dots(A->view(), p, q, nullptr, dots, red, A->spmv_grid(), s));
     HIP_TRY(hipStreamSynchronize(s));
     if (dots_host) {
         const volatile double *d = A->h_dots;
-        if (d[KMAX] != 1.0)
+        if (d[HOST_DONE] != 1.0 || d[HOST_FAULT] != 0.0)
             return scratch_fault(A->st, A->partials, s);
         dots_host[0] = d[0];
         dots_host[1] = d[1];
     }
+    return FK_OK;
+}
+
+extern "C" fk_status fk_csr_test_fault(fk_csr A, int32_t group)
+{
+    if (!A)
+        return fail(FK_E_ARG, "NULL matrix");
+    if (group < 0 || group >= GMAX / RGROUP)
+        return fail(FK_E_ARG, "group must be in [0, %d)", GMAX / RGROUP);
+    A->test_fault = group + 1;
     return FK_OK;
 }
 

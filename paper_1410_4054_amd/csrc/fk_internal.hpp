@@ -141,10 +141,14 @@ struct RedArgs {
     // partials of `kpub` dots (0: none), appended after the kernel's own dots.
     int32_t npub = 0;
     int32_t kpub = 0;
-    // Pinned host memory (or null): the rounded dots [KMAX], then 1.0 once
-    // they are there.
+    // Pinned host memory (or null), zero before the launch: the rounded dots
+    // [KMAX], 1.0 at HOST_DONE once they are there, and 1.0 at HOST_FAULT from
+    // any leader that gave up (one below the top leaves an incomplete sum that
+    // the top leader cannot tell from a whole one).  npub = 1 + a group makes
+    // that group's leader report so.
     double *host = nullptr;
 };
+constexpr int HOST_DONE = KMAX, HOST_FAULT = KMAX + 1, HOST_WORDS = KMAX + 2;
 
 // Rows per slice of the sliced layout: one wave64, one row per lane.
 constexpr int SLICE = 64;

@@ -265,6 +265,17 @@ __device__ __forceinline__ bool collect(const double *base, int stride, int coun
     }
 }
 
+// A leader ran out of polls: the sums it hands on are incomplete, so the
+// result is void wherever the reduction leaves it, however many of the other
+// leaders finish.
+__device__ __forceinline__ void give_up(const RedArgs &red)
+{
+    red.st->red_fault = 1;
+    red.st->status = ST_BREAKDOWN;
+    if (red.host)
+        red.host[HOST_FAULT] = 1.0;
+}
+
 template <int K, typename ACC = AccDD>
 __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedArgs &red, int g, int G)
 {
@@ -331,6 +342,8 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
     const int kt = K + kpub;
     T mem[K];
     bool done = collect<K, ACC>(part1 + 2 * (size_t)gbase, GMAX, gsize, own, v, mem);
+    if (red.host && red.npub == grp + 1)  // asked for: fk_csr_test_fault
+        done = false;
     T acc[KT];
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -366,10 +379,8 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
                     ACC::store(part2 + 2 * ((size_t)k * RNGROUPS_MAX + grp), acc[k]);
                 // a leader that gave up voids the reduction and stops the
                 // solve; the top leader still receives a sum and ends
-                if (!done) {
-                    red.st->red_fault = 1;
-                    red.st->status = ST_BREAKDOWN;
-                }
+                if (!done)
+                    give_up(red);
             }
             // the members' slots are free again for the next launch
             if (lane < gsize && lane != own) {
@@ -401,8 +412,7 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
     asm volatile("" ::"v"(state_line));
     if (lane == 0) {
         if (!done) {
-            red.st->red_fault = 1;
-            red.st->status = ST_BREAKDOWN;
+            give_up(red);
             return;
         }
         double d[KT > 0 ? KT : 1];
@@ -413,7 +423,7 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
         if (red.host) {
             for (int k = 0; k < kt; ++k)
                 red.host[k] = d[k];
-            red.host[KMAX] = 1.0;
+            red.host[HOST_DONE] = 1.0;
         }
     }
 }

@@ -117,6 +117,7 @@ def lib():
             "fk_solver_uses_small": [vp, P(i32)],
             "fk_get_refinements": [vp, P(i32)],
             "fk_spmv": [vp, vp, vp, P(f64), vp],
+            "fk_csr_test_fault": [vp, i32],
             "fk_spmv_time": [vp, vp, vp, i32, i32, P(f64), vp],
             "fk_spmv32": [vp, vp, vp, i32, P(f64), vp],
             "fk_dot": [i64, vp, vp, P(f64), vp],
@@ -158,7 +159,8 @@ def exported_symbols() -> list[str]:
         "fk_csr_set_layout", "fk_csr_set_stream", "fk_csr_stream",
         "fk_solver_create", "fk_solve", "fk_get_iterations", "fk_get_residual",
         "fk_get_residual_history", "fk_get_scalars", "fk_get_kernel_times",
-        "fk_solver_destroy", "fk_solver_uses_small", "fk_get_refinements", "fk_spmv", "fk_spmv_time",
+        "fk_solver_destroy", "fk_solver_uses_small", "fk_get_refinements", "fk_spmv", "fk_csr_test_fault",
+        "fk_spmv_time",
         "fk_spmv32", "fk_dot",
         "fk_copy",
         "fk_axpby", "fk_net_num_weights", "fk_net_create", "fk_net_destroy", "fk_net_get_weights",
@@ -266,6 +268,11 @@ class Matrix:
         on, sw = ctypes.c_int32(), ctypes.c_int32()
         _check(lib().fk_csr_stream(self._h, ctypes.byref(on), ctypes.byref(sw)), "fk_csr_stream")
         return bool(on.value), bool(sw.value)
+
+    def test_fault(self, group: int):
+        """For tests: the next spmv(dots=True) finds that the reduction's leader
+        of this group of 64 workgroups gave up."""
+        _check(lib().fk_csr_test_fault(self._h, int(group)), "fk_csr_test_fault")
 
     def close(self):
         if self._h:
