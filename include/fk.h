@@ -370,6 +370,27 @@ fk_status fk_solver_destroy(fk_solver S);
 /* *small = 1 if fk_solve runs the single-workgroup solver, else 0. */
 fk_status fk_solver_uses_small(fk_solver S, int32_t *small);
 
+/*
+ * The resident path (see fk_solver_create) of a solver: *workgroups and *rows
+ * (per workgroup) of its launch, 0 when the solver has none; *launches: how
+ * many such launches the last fk_solve ran (0: another path solved it; a solve
+ * takes one per 8192 iterations); *declined = 1 if one of them ended without a
+ * start, because its workgroups did not all get onto the chip, and the
+ * multi-kernel path went on from there.
+ */
+fk_status fk_solver_resident(fk_solver S, int32_t *workgroups, int32_t *rows, int32_t *launches,
+                             int32_t *declined);
+
+/*
+ * For tests of the resident path: decline > 0 tells that launch of every
+ * further solve (1 = the first) not to start (a single workgroup always does);
+ * 0 none.  next_tag != 0: the number from which the next launch counts its
+ * products (a solver's first launch counts from 1; they start at 1 again before
+ * they exceed 32 bits).  FK_E_STATE when the solver is not resident, FK_E_ARG
+ * for a negative launch or a number below the solver's own.
+ */
+fk_status fk_solver_test_resident(fk_solver S, int32_t decline, uint32_t next_tag);
+
 /* FK_CG_MIXED: refinement sweeps (corrections x += d) of the last solve;
  * 0 for the other methods. */
 fk_status fk_get_refinements(fk_solver S, int32_t *sweeps);

@@ -921,6 +921,8 @@ struct fk_solver_s {
     char *res_mem = nullptr;
     size_t res_words = 0;  // tagged words at its start, zero before the first tag
     uint32_t res_epoch = 1;
+    int32_t res_launches = 0, res_declined = 0;  // of the last solve: run, declined
+    int32_t test_decline = 0;  // the launch of a solve that is told not to start, 0: none
     // FK_CG_MIXED: FP32 inner vectors and matrix values; the refinement's
     // own state (st is the inner solver's); sweeps of the last solve.
     bool mixed = false;
@@ -1971,6 +1973,7 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
             S->res_epoch = 1;
         }
         a.epoch = S->res_epoch;
+        a.refuse = S->test_decline == S->res_launches + 1;
         S->res_epoch += RES_TAGS;
         hipError_t e = launch_resident(S->res, a, S->stream);
         if (e != hipSuccess)
@@ -1982,10 +1985,12 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
         if (ctl.fault == a.epoch)
             return reduction_fault(S);
         if (ctl.declined == a.epoch) {
+            S->res_declined = 1;
             fk_status fs = run_batches(S, b, x, S->o.rtol, S->o.max_iter, S->hist_cap, false, false, a.resume != 0,
                                        a.resume ? S->last.it : 0);
             return fs != FK_OK ? fs : finish_solve(S);
         }
+        ++S->res_launches;
         if (S->last.status != ST_RUNNING)
             break;
         a.resume = 1;
@@ -2003,6 +2008,7 @@ extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
         return fail(FK_E_ARG, "NULL argument");
     S->solved = false;
     S->sweeps = 0;
+    S->res_launches = S->res_declined = 0;
     if (S->red_dirty) {
         HIP_TRY(launch_red_init(S->partials, S->stream));
         S->red_dirty = false;
@@ -2254,6 +2260,33 @@ extern "C" fk_status fk_solver_uses_small(fk_solver S, int32_t *small)
     if (!S || !small)
         return fail(FK_E_ARG, "NULL argument");
     *small = S->small ? 1 : 0;
+    return FK_OK;
+}
+
+extern "C" fk_status fk_solver_resident(fk_solver S, int32_t *workgroups, int32_t *rows, int32_t *launches,
+                                        int32_t *declined)
+{
+    if (!S || !workgroups || !rows || !launches || !declined)
+        return fail(FK_E_ARG, "NULL argument");
+    *workgroups = S->resident ? S->res.groups : 0;
+    *rows = S->resident ? S->res.rows : 0;
+    *launches = S->res_launches;
+    *declined = S->res_declined;
+    return FK_OK;
+}
+
+extern "C" fk_status fk_solver_test_resident(fk_solver S, int32_t decline, uint32_t next_tag)
+{
+    if (!S || decline < 0)
+        return fail(FK_E_ARG, "NULL solver or decline < 0");
+    if (!S->resident)
+        return fail(FK_E_STATE, "not a resident solver");
+    // (tags only grow: a word may still carry an earlier one)
+    if (next_tag != 0 && next_tag < S->res_epoch)
+        return fail(FK_E_ARG, "the next tag is already %u", S->res_epoch);
+    S->test_decline = decline;
+    if (next_tag != 0)
+        S->res_epoch = next_tag;
     return FK_OK;
 }
 

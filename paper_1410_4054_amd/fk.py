@@ -115,6 +115,8 @@ def lib():
             "fk_get_kernel_times": [vp, P(f64), P(i32), i32],
             "fk_solver_destroy": [vp],
             "fk_solver_uses_small": [vp, P(i32)],
+            "fk_solver_resident": [vp, P(i32), P(i32), P(i32), P(i32)],
+            "fk_solver_test_resident": [vp, i32, ctypes.c_uint32],
             "fk_get_refinements": [vp, P(i32)],
             "fk_spmv": [vp, vp, vp, P(f64), vp],
             "fk_csr_test_fault": [vp, i32],
@@ -159,7 +161,8 @@ def exported_symbols() -> list[str]:
         "fk_csr_set_layout", "fk_csr_set_stream", "fk_csr_stream",
         "fk_solver_create", "fk_solve", "fk_get_iterations", "fk_get_residual",
         "fk_get_residual_history", "fk_get_scalars", "fk_get_kernel_times",
-        "fk_solver_destroy", "fk_solver_uses_small", "fk_get_refinements", "fk_spmv", "fk_csr_test_fault",
+        "fk_solver_destroy", "fk_solver_uses_small", "fk_solver_resident", "fk_solver_test_resident",
+        "fk_get_refinements", "fk_spmv", "fk_csr_test_fault",
         "fk_spmv_time",
         "fk_spmv32", "fk_dot",
         "fk_copy",
@@ -412,6 +415,18 @@ class Solver:
         v = ctypes.c_int32()
         _check(lib().fk_solver_uses_small(self._h, ctypes.byref(v)), "fk_solver_uses_small")
         return bool(v.value)
+
+    def resident(self) -> tuple[int, int, int, bool]:
+        """(workgroups, rows per workgroup) of the solver's resident launch, 0
+        for none; such launches that ran in the last solve; one was declined."""
+        v = [ctypes.c_int32() for _ in range(4)]
+        _check(lib().fk_solver_resident(self._h, *map(ctypes.byref, v)), "fk_solver_resident")
+        return v[0].value, v[1].value, v[2].value, bool(v[3].value)
+
+    def test_resident(self, decline: int = 0, next_tag: int = 0):
+        """For tests: the launch of every further solve that does not start; the
+        number from which the next launch counts its products."""
+        _check(lib().fk_solver_test_resident(self._h, int(decline), int(next_tag)), "fk_solver_test_resident")
 
     def iterations(self) -> int:
         k = ctypes.c_int32()
