@@ -1967,9 +1967,12 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
     a.resume = 0;
     ResCtl ctl{};
     for (;;) {
-        if (S->res_epoch > UINT32_MAX - RES_TAGS) {  // start the tags again
+        if (S->res_epoch > UINT32_MAX - RES_TAGS) {
+            // Start the tags again: no word, and no launch given up or void,
+            // may carry one of the numbers to come.
             HIP_TRY(launch_clear(reinterpret_cast<double *>(S->res_mem), (int64_t)(S->res_words / 8), S->grid_vec,
                                  S->stream));
+            HIP_TRY(launch_clear(reinterpret_cast<double *>(S->st + 1), (int64_t)(sizeof(DevState) / 8), 1, S->stream));
             S->res_epoch = 1;
         }
         a.epoch = S->res_epoch;

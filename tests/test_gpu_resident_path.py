@@ -174,3 +174,35 @@ def test_scalars_after_declined_continuation(device):
     a, b = out[0][1], out[1][1]  # alpha, beta, (omega: BiCGStab's), <r,r>
     assert len(a) == len(b) > 8192
     assert np.array_equal(a[:, 3], b[:, 3]) and np.array_equal(a[:-1, :2], b[:-1, :2])
+
+
+@pytest.mark.parametrize("method", METHODS)
+def test_tags_start_again(method, device):
+    """The 32-bit tags run out: between two solves, with a launch declined under
+    the number that now comes again, and between two launches of a solve."""
+    A = P.heat2d(100)
+    b = P.rhs_uniform(A.n, 5)
+    bd = dev(b)
+    ref = _oracle(A, b, method, rtol=1e-8)
+    S = _solver(A, method)
+    S.test_resident(decline=1)  # the solver's first launch: number 1
+    _same(S, bd, ref)
+    assert S.resident()[2:] == (0, True)
+    for last in (2**32 - 1, 2**32 - 16392, 2**32 - 16393):  # the last two: one launch short of it, and just enough
+        print(f"\n[case] tags {method} from {last}", flush=True)
+        S = S if last == 2**32 - 1 else _solver(A, method)
+        S.test_resident(next_tag=last)
+        for _ in range(3):
+            _same(S, bd, ref)
+            assert S.resident()[2:] == (1, False)
+    A = _long(method)
+    bd = dev(P.rhs_uniform(A.n, 11))
+    out = []
+    for tag in (1, 2**32 - 1 - 16392):
+        S = _solver(A, method, rtol=0.0, max_iter=8195)
+        S.test_resident(next_tag=tag)
+        x = dev(np.zeros(A.n))
+        S.solve(bd, x)
+        assert S.resident()[2:] == (2, False)
+        out.append((host(x), S.history()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
