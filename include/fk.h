@@ -260,7 +260,8 @@ fk_status fk_csr_stream(fk_csr A, int32_t *streaming, int32_t *sweep);
  * solver).
  * FK_FLAG_GRAPH and FK_FLAG_PROFILE, which replay or time the launches of
  * the multi-kernel path, and the streaming mode keep to that path; so does a
- * solve whose workgroups do not find room on the device beside other work.
+ * solve whose workgroups do not find room on the device beside other work, and
+ * after it the next 1, 2, 4, .. 64 solves on that solver, until one starts.
  */
 fk_status fk_solver_create(fk_csr A, const fk_opts *o, void *hip_stream, fk_solver *out);
 
@@ -383,11 +384,12 @@ fk_status fk_solver_resident(fk_solver S, int32_t *workgroups, int32_t *rows, in
 
 /*
  * For tests of the resident path: decline > 0 tells that launch of every
- * further solve (1 = the first) not to start (a single workgroup always does);
- * 0 none.  next_tag != 0: the number from which the next launch counts its
- * products (a solver's first launch counts from 1; they start at 1 again before
- * they exceed 32 bits).  FK_E_STATE when the solver is not resident, FK_E_ARG
- * for a negative launch or a number below the solver's own.
+ * further solve (1 = the first) not to start (a single workgroup always does),
+ * 0 none; what was declined before is forgotten.  next_tag != 0: the number
+ * from which the next launch counts its products (a solver's first launch
+ * counts from 1; they start at 1 again before they exceed 32 bits).
+ * FK_E_STATE when the solver is not resident, FK_E_ARG for a negative launch or
+ * a number below the solver's own.
  */
 fk_status fk_solver_test_resident(fk_solver S, int32_t decline, uint32_t next_tag);
 

@@ -922,6 +922,10 @@ struct fk_solver_s {
     size_t res_words = 0;  // tagged words at its start, zero before the first tag
     uint32_t res_epoch = 1;
     int32_t res_launches = 0, res_declined = 0;  // of the last solve: run, declined
+    // Solves that stay off the path after a declined start, and how many the
+    // last one was followed by: twice as many after each in a row, up to
+    // RES_REST_MAX.
+    int32_t res_rest = 0, res_rests = 0;
     int32_t test_decline = 0;  // the launch of a solve that is told not to start, 0: none
     // FK_CG_MIXED: FP32 inner vectors and matrix values; the refinement's
     // own state (st is the inner solver's); sweeps of the last solve.
@@ -1086,6 +1090,11 @@ static std::atomic<int> &resident_units(int device)
 // Iterations of one resident launch; longer solves continue in the next.
 constexpr int RES_CHUNK = 8192;
 constexpr uint32_t RES_TAGS = 2 * RES_CHUNK + 8;  // tags a launch may use: two products an iteration
+// A declined start has waited (about 20 ms) for workgroups that found no room,
+// where a solve takes 0.2 to 17 ms.  Whatever holds the compute units (a stream
+// restricted to some of them, another stream's long kernel) is likely to hold
+// them at the next solve too, so the solver then goes without for a while.
+constexpr int32_t RES_REST_MAX = 64;
 // Fewest unknowns of a solve on several resident workgroups; below, one
 // workgroup solves alone (BiCGStab up to 2048 unknowns, the one-kernel CG up
 // to 3072, CG up to 4096), or the caller asked for the multi-kernel path.  us
@@ -1989,11 +1998,14 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
             return reduction_fault(S);
         if (ctl.declined == a.epoch) {
             S->res_declined = 1;
+            S->res_rests = std::min(std::max(1, 2 * S->res_rests), RES_REST_MAX);
+            S->res_rest = S->res_rests;
             fk_status fs = run_batches(S, b, x, S->o.rtol, S->o.max_iter, S->hist_cap, false, false, a.resume != 0,
                                        a.resume ? S->last.it : 0);
             return fs != FK_OK ? fs : finish_solve(S);
         }
         ++S->res_launches;
+        S->res_rests = 0;
         if (S->last.status != ST_RUNNING)
             break;
         a.resume = 1;
@@ -2029,7 +2041,9 @@ extern "C" fk_status fk_solve(fk_solver S, const double *b, double *x)
     if (S->gmres)
         return solve_gmres(S, b, x, profile);
 
-    if (S->resident) {
+    if (S->resident && S->res_rest > 0) {
+        --S->res_rest;
+    } else if (S->resident) {
         std::atomic<int> &units = resident_units(S->A->device);
         if (units.fetch_add(S->res.groups) + S->res.groups <= S->A->cus) {
             const fk_status fs = solve_resident(S, b, x);
@@ -2288,6 +2302,7 @@ extern "C" fk_status fk_solver_test_resident(fk_solver S, int32_t decline, uint3
     if (next_tag != 0 && next_tag < S->res_epoch)
         return fail(FK_E_ARG, "the next tag is already %u", S->res_epoch);
     S->test_decline = decline;
+    S->res_rest = S->res_rests = 0;
     if (next_tag != 0)
         S->res_epoch = next_tag;
     return FK_OK;

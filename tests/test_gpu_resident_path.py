@@ -206,3 +206,27 @@ def test_tags_start_again(method, device):
         assert S.resident()[2:] == (2, False)
         out.append((host(x), S.history()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_declined_starts_are_remembered(device):
+    """After a declined start a solver leaves the path for 1, 2, 4, ... 64 solves
+    before it tries again; a launch that starts ends that."""
+    A = P.heat2d(100)
+    b = P.rhs_uniform(A.n, 5)
+    bd = dev(b)
+    ref = _oracle(A, b, "cg_pipelined", rtol=1e-8)
+    S = _solver(A, "cg_pipelined")
+
+    def solve():
+        _same(S, bd, ref)
+        return S.resident()[2:]
+
+    S.test_resident(decline=1)
+    for rest in (1, 2, 4, 8, 16, 32, 64, 64):
+        print(f"\n[case] declined, then {rest} solves without", flush=True)
+        assert solve() == (0, True)
+        assert [solve() for _ in range(rest)] == [(0, False)] * rest
+    S.test_resident(decline=0)
+    assert solve() == (1, False) and solve() == (1, False)
+    S.test_resident(decline=1)
+    assert solve() == (0, True) and solve() == (0, False) and solve() == (0, True)
