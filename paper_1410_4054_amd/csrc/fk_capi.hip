@@ -153,7 +153,7 @@ struct fk_csr_s {
     int64_t stride1 = 0, stride2 = 0;  // slots: the largest offset (2), the largest at most half of it (1)
     int32_t layout = FK_LAYOUT_ROW_BLOCKS;  // layout the products read
     // scratch reduction state for fk_spmv / fk_spmv32, and pinned memory that
-    // takes fk_spmv's dots (RedArgs::host)
+    // takes fk_spmv's dots (D_HOST)
     double *h_dots = nullptr;
     int32_t test_fault = 0;  // 1 + the group of fk_csr_test_fault
     DevState *st = nullptr;
@@ -2402,7 +2402,7 @@ extern "C" fk_status fk_spmv(fk_csr A, const double *p, double *q, double *dots_
     if ((const void *)p == (const void *)q)
         return fail(FK_E_ARG, "p and q must not alias");
     hipStream_t s = (hipStream_t)hip_stream;
-    const int dots = dots_host ? (D_YV | D_YY) : 0;
+    const int dots = dots_host ? (D_YV | D_YY | D_HOST) : 0;
     RedArgs red{A->st, A->partials, nullptr, nullptr, FIN_NONE, RUN_ALWAYS};
     if (dots_host) {
         // The reduction leaves the dots in pinned memory; copying the state to
@@ -2410,7 +2410,7 @@ extern "C" fk_status fk_spmv(fk_csr A, const double *p, double *q, double *dots_
         // rows: 33 us, 25 without).
         A->h_dots[HOST_DONE] = 0.0;
         A->h_dots[HOST_FAULT] = 0.0;
-        red.host = A->h_dots;
+        red.hist = A->h_dots;
         red.npub = A->test_fault;
         A->test_fault = 0;
     }

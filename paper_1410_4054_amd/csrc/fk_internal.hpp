@@ -141,13 +141,14 @@ struct RedArgs {
     // partials of `kpub` dots (0: none), appended after the kernel's own dots.
     int32_t npub = 0;
     int32_t kpub = 0;
-    // Pinned host memory (or null), zero before the launch: the rounded dots
-    // [KMAX], 1.0 at HOST_DONE once they are there, and 1.0 at HOST_FAULT from
-    // any leader that gave up (one below the top leaves an incomplete sum that
-    // the top leader cannot tell from a whole one).  npub = 1 + a group makes
-    // that group's leader report so.
-    double *host = nullptr;
 };
+
+// The products of fk_spmv (D_HOST) leave their dots in pinned host memory too:
+// RedArgs::hist points to HOST_WORDS zeros that take the rounded dots [KMAX],
+// 1.0 at HOST_DONE once they are there, and 1.0 at HOST_FAULT from any leader
+// that gave up (one below the top leaves an incomplete sum that the top leader
+// cannot tell from a whole one).  npub = 1 + a group makes that group's leader
+// report so.
 constexpr int HOST_DONE = KMAX, HOST_FAULT = KMAX + 1, HOST_WORDS = KMAX + 2;
 
 // Rows per slice of the sliced layout: one wave64, one row per lane.
@@ -218,6 +219,7 @@ enum DotBits : int32_t {
     D_YV = 1,  // <y, v>
     D_YY = 2,  // <y, y>
     D_YW = 4,  // <y, w>
+    D_HOST = 8,  // (with D_YV | D_YY) the dots also to pinned host memory
 };
 
 // Profiling: when set, the next kernel launched by a wrapper below carries

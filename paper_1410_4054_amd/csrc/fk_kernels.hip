@@ -268,15 +268,19 @@ __device__ __forceinline__ bool collect(const double *base, int stride, int coun
 // A leader ran out of polls: the sums it hands on are incomplete, so the
 // result is void wherever the reduction leaves it, however many of the other
 // leaders finish.
+template <bool HOST>
 __device__ __forceinline__ void give_up(const RedArgs &red)
 {
     red.st->red_fault = 1;
     red.st->status = ST_BREAKDOWN;
-    if (red.host)
-        red.host[HOST_FAULT] = 1.0;
+    if constexpr (HOST)
+        red.hist[HOST_FAULT] = 1.0;
 }
 
-template <int K, typename ACC = AccDD>
+// HOST: the dots also to pinned host memory.  An instance of its own, so that
+// the end of every other reduction, which each iteration of a solve waits for,
+// does not ask for it.
+template <int K, typename ACC = AccDD, bool HOST = false>
 __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedArgs &red, int g, int G)
 {
     using T = typename ACC::T;
@@ -342,8 +346,8 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
     const int kt = K + kpub;
     T mem[K];
     bool done = collect<K, ACC>(part1 + 2 * (size_t)gbase, GMAX, gsize, own, v, mem);
-    if (red.host && red.npub == grp + 1)  // asked for: fk_csr_test_fault
-        done = false;
+    if constexpr (HOST)
+        done = done && red.npub != grp + 1;  // (asked for: fk_csr_test_fault)
     T acc[KT];
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -380,7 +384,7 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
                 // a leader that gave up voids the reduction and stops the
                 // solve; the top leader still receives a sum and ends
                 if (!done)
-                    give_up(red);
+                    give_up<HOST>(red);
             }
             // the members' slots are free again for the next launch
             if (lane < gsize && lane != own) {
@@ -412,7 +416,7 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
     asm volatile("" ::"v"(state_line));
     if (lane == 0) {
         if (!done) {
-            give_up(red);
+            give_up<HOST>(red);
             return;
         }
         double d[KT > 0 ? KT : 1];
@@ -420,10 +424,10 @@ __device__ __forceinline__ void reduce_point(typename ACC::T (&v)[K], const RedA
         for (int k = 0; k < KT; ++k)
             d[k] = ACC::round(acc[k]);
         finalize(red.st, red.fin, d, kt, red.hist, red.scal);
-        if (red.host) {
-            for (int k = 0; k < kt; ++k)
-                red.host[k] = d[k];
-            red.host[HOST_DONE] = 1.0;
+        if constexpr (HOST) {
+            for (int k = 0; k < K; ++k)
+                red.hist[k] = d[k];
+            red.hist[HOST_DONE] = 1.0;
         }
     }
 }
@@ -574,7 +578,7 @@ __global__ __launch_bounds__(WG, FK_SPMV_MIN_WAVES) void k_csr_rows(DevCsr A, Ro
         }
     }
     if constexpr (K > 0)
-        reduce_point<KA>(acc, red, g, G);
+        reduce_point<KA, AccDD, (DOTS & D_HOST) != 0>(acc, red, g, G);
 }
 
 // ------------------------------------------------ sliced-layout products
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(WG, FK_SPMV_MIN_WAVES) void k_sell_rows(DevCsr A, R
         }
     }
     if constexpr (K > 0)
-        reduce_point<KA>(acc, red, g, G);
+        reduce_point<KA, AccDD, (DOTS & D_HOST) != 0>(acc, red, g, G);
 }
 
 // out[e] = vals[map[e]], or 0 where map[e] < 0: the values of the sliced
@@ -2367,6 +2371,7 @@ hipError_t launch_spmv_dots(const DevCsr &A, const double *v, double *y, const d
     case 0: return launch_rows<ROW_SPMV, 0>(A, io, red, grid, s);
     case D_YV: return launch_rows<ROW_SPMV, D_YV>(A, io, red, grid, s);
     case D_YV | D_YY: return launch_rows<ROW_SPMV, D_YV | D_YY>(A, io, red, grid, s);
+    case D_YV | D_YY | D_HOST: return launch_rows<ROW_SPMV, D_YV | D_YY | D_HOST>(A, io, red, grid, s);
     case D_YW: return launch_rows<ROW_SPMV, D_YW>(A, io, red, grid, s);
     case D_YV | D_YY | D_YW: return launch_rows<ROW_SPMV, D_YV | D_YY | D_YW>(A, io, red, grid, s);
     default: return hipErrorInvalidValue;
