@@ -42,3 +42,33 @@ def test_spmv_test_fault_arguments(device):
         with pytest.raises(fk.FkError) as e:
             M.test_fault(group)
         assert e.value.status == fk.E_ARG
+
+
+def test_spmv_dots_of_many_matrices(device):
+    """The pinned words that the dots arrive in are shared out among the
+    matrices, 64 to a page: three pages in use, given back in another order and
+    taken again."""
+    rng = np.random.default_rng(2)
+    mats = [P.poisson2d(4 + i % 7) for i in range(150)]
+    ps = [rng.uniform(-1, 1, A.n) for A in mats]
+    want = []
+    for A, p in zip(mats, ps):
+        q = oracle.spmv(A, p)
+        want.append((float(p @ q), float(q @ q)))
+    Ms = [fk.Matrix(A) for A in mats]
+
+    def check(i):
+        got = fk.spmv(Ms[i], dev(ps[i]), dev(np.zeros(mats[i].n)), dots=True)
+        # (numpy's sums of at most 100 products: within 100 roundings)
+        assert np.allclose(got, want[i], rtol=0, atol=100 * 2.0 ** -53 * 8 * mats[i].n), i
+
+    for i in range(150):
+        check(i)
+    for i in rng.permutation(150)[:120]:
+        Ms[i].close()
+        Ms[i] = None
+    for i in range(150):
+        if Ms[i] is None:
+            Ms[i] = fk.Matrix(mats[i])
+    for i in rng.permutation(150):
+        check(int(i))
