@@ -484,6 +484,16 @@ fk_status fk_net_get_weights(fk_net N, float *weights_host, int64_t count);
 /* Replace the weights and reset the optimiser state. */
 fk_status fk_net_set_weights(fk_net N, const float *weights_host, int64_t count);
 
+/*
+ * Workspace (kept, and grown to the largest grid): the layers' activations, 32
+ * bytes per grid point each, and as much for the gradient of each hidden layer's
+ * output; where memory has no room for those, two gradient planes are used in
+ * turn, with the same results in up to 25 % more time.  fk_net_set_plane_limit:
+ * use two also where more would take over `bytes` >= 0 in all (a new network:
+ * no limit).  Waits for the device and frees the workspace.
+ */
+fk_status fk_net_set_plane_limit(fk_net N, int64_t bytes);
+
 /* Raw network output N(r) for r = b - A (2 u_m - u_{m-1}) into device
  * float32 y[n].  Synchronous. */
 fk_status fk_net_forward(fk_net N, fk_csr A, int32_t nx, int32_t ny, const double *b_dev,

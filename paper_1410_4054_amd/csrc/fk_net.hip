@@ -429,6 +429,7 @@ static_assert(DXC / 2 % 64 == 8 && DGC / 2 % 64 == 8, "bank spread of the channe
 
 struct DwArgs {
     int nx, ny, layers;
+    int first;                        // layer of blockIdx.y = 0
     const uint16_t *act[MAX_LAYERS];  // input of layer l: [n][4] (l = 0) or [n][16]
     const uint16_t *g[MAX_LAYERS];    // gradient of its output: [n][4] (last) or [n][16]
     float *partials;                  // [layer][gridDim.x][DW_ELEMS]
@@ -525,12 +526,12 @@ __device__ __forceinline__ void dw_layer(const DwArgs &d, int l, uint32_t *lds)
         out[e] = red[e];
 }
 
-// All layers in one launch: blockIdx.y is the layer.
+// Several layers in one launch: blockIdx.y counts them from d.first.
 __global__ __launch_bounds__(NWG) void k_dw(DwArgs d)
 {
     __shared__ __align__(16) uint32_t lds[CH * (DXC + DGC) / 2];
     static_assert(CH * (DXC + DGC) / 2 >= DW_ELEMS, "the wave sums reuse the staged tiles");
-    const int l = blockIdx.y;
+    const int l = d.first + (int)blockIdx.y;
     if (l == 0)
         dw_layer<4, 16>(d, l, lds);
     else if (l == d.layers - 1)
@@ -786,7 +787,9 @@ struct fk_net_s {
     int64_t cap = 0;
     uint16_t *feat = nullptr;             // [n][4]
     uint16_t *act[MAX_LAYERS] = {};       // act[l], l = 1..L-1: [n][16]
-    uint16_t *g16[MAX_LAYERS] = {};       // g16[l], l = 0..L-2: [n][16] gradient of layer l's output
+    uint16_t *g16[MAX_LAYERS] = {};       // [n][16] gradients of the hidden layers' outputs (grad_plane)
+    int planes = 0;                       // ... of which there are L-1, or two
+    size_t plane_limit = SIZE_MAX;        // bytes they may take where there are more than two
     uint16_t *g4 = nullptr;               // [n][4] output gradient
     float *y = nullptr, *target = nullptr;
     double *rbuf = nullptr;
@@ -870,6 +873,14 @@ hipError_t dalloc(T **p, size_t count)
     return hipMalloc(reinterpret_cast<void **>(p), std::max<size_t>(count, 1) * sizeof(T));
 }
 
+// The plane of the gradient of layer l's output, l = 0 .. L-2.  With a plane for
+// each hidden layer the weight gradients of all layers are one launch at the
+// end.  Where device memory (or the caller's limit) has no room for them, two
+// planes are used in turn, and a layer's weight gradient is launched before its
+// plane is overwritten: 512 workgroups at a time leave half the chip idle (eight
+// layers on 2000^2: 2.25 ms, 1.84 with all planes; 1100^2: 0.82 and 0.71).
+uint16_t *grad_plane(fk_net N, int l) { return N->g16[l % N->planes]; }
+
 fk_status ensure_workspace(fk_net N, int64_t n)
 {
     if (N->cap >= n)
@@ -880,8 +891,6 @@ fk_status ensure_workspace(fk_net N, int64_t n)
     e = e ? e : dalloc(&N->feat, un * 4);
     for (int l = 1; l < N->meta.layers && e == hipSuccess; ++l)
         e = dalloc(&N->act[l], un * 16);
-    for (int l = 0; l < N->meta.layers - 1 && e == hipSuccess; ++l)
-        e = dalloc(&N->g16[l], un * 16);
     e = e ? e : dalloc(&N->g4, un * 4);
     e = e ? e : dalloc(&N->y, un);
     e = e ? e : dalloc(&N->target, un);
@@ -893,6 +902,19 @@ fk_status ensure_workspace(fk_net N, int64_t n)
     e = e ? e : dalloc(&N->loss, 1);
     e = e ? e : dalloc(&N->flag, 1);
     e = e ? e : dalloc(&N->xtmp, un);
+    // the gradient planes last: as many as there is room for
+    const int want = N->meta.layers - 1, least = std::min(want, 2);
+    N->planes = want > least && un > N->plane_limit / 32 / (size_t)want ? least : want;
+    for (int l = 0; l < N->planes && e == hipSuccess; ++l) {
+        e = dalloc(&N->g16[l], un * 16);
+        if (e == hipErrorOutOfMemory && l >= least) {
+            (void)hipGetLastError();
+            while (l > least)
+                dfree(N->g16[--l]);
+            N->planes = least;
+            e = hipSuccess;
+        }
+    }
     if (e != hipSuccess) {
         release_workspace(N);
         return e == hipErrorOutOfMemory ? net_fail(FK_E_OOM, "network workspace: out of device memory")
@@ -955,9 +977,9 @@ hipError_t forward(fk_net N, int nx, int ny, int64_t n, const float *target, hip
 }
 
 // Normalised features and target of one training sample, forward, loss and
-// backward: the gradient lands in N->grad, the loss in N->loss.  The
-// backward data pass keeps every layer's gradient plane, so that the weight
-// gradients of all layers are one launch after it.
+// backward: the gradient lands in N->grad, the loss in N->loss.  Where the
+// backward data pass keeps every layer's gradient plane, the weight gradients
+// of all layers are one launch after it.
 hipError_t loss_and_gradient(fk_net N, const DevCsr &A, int nx, int ny, const double *b, const double *um,
                              const double *um1, const double *unext, hipStream_t s)
 {
@@ -979,18 +1001,24 @@ hipError_t loss_and_gradient(fk_net N, const DevCsr &A, int nx, int ny, const do
     d.partials = N->dwpart;
     d.act[0] = N->feat;
     d.g[L - 1] = N->g4;
+    const int gd = grid_for(tiles_of(nx, ny, DTX, DTY), 1, DW_GRID);
+    const bool all = N->planes == L - 1;
     for (int l = L - 1; l > 0; --l) {
         d.act[l] = N->act[l];
-        d.g[l - 1] = N->g16[l - 1];
-        ConvArgs a{nx, ny, n, d.g[l], N->packed + N->meta.l[l].pt, N->g16[l - 1], N->act[l], nullptr, nullptr,
+        d.g[l - 1] = grad_plane(N, l - 1);
+        if (!all) {
+            d.first = l;
+            hipLaunchKernelGGL(k_dw, dim3(gd, 1), dim3(NWG), 0, s, d);
+        }
+        ConvArgs a{nx, ny, n, d.g[l], N->packed + N->meta.l[l].pt, grad_plane(N, l - 1), N->act[l], nullptr, nullptr,
                    nullptr, N->meta.relu};
         if (l == L - 1)
             hipLaunchKernelGGL((k_conv<4, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
         else
             hipLaunchKernelGGL((k_conv<16, EPI_MASK>), dim3(gc), dim3(NWG), 0, s, a);
     }
-    const int gd = grid_for(tiles_of(nx, ny, DTX, DTY), 1, DW_GRID);
-    hipLaunchKernelGGL(k_dw, dim3(gd, L), dim3(NWG), 0, s, d);
+    d.first = 0;
+    hipLaunchKernelGGL(k_dw, dim3(gd, all ? L : 1), dim3(NWG), 0, s, d);
     hipLaunchKernelGGL(k_grad_reduce, dim3(DWR, L + 1), dim3(NWG), 0, s, N->dwpart, gd, N->meta, N->grad,
                        N->losspart, gc, n, N->loss);
     return hipGetLastError();
@@ -1075,6 +1103,16 @@ extern "C" fk_status fk_net_get_weights(fk_net N, float *out, int64_t count)
     if (!N || !out || count != N->meta.nweights)
         return net_fail(FK_E_ARG, "bad argument");
     NET_HIP(hipMemcpy(out, N->w, (size_t)count * 4, hipMemcpyDeviceToHost));
+    return FK_OK;
+}
+
+extern "C" fk_status fk_net_set_plane_limit(fk_net N, int64_t bytes)
+{
+    if (!N || bytes < 0)
+        return net_fail(FK_E_ARG, "bad argument");
+    N->plane_limit = (size_t)bytes;
+    NET_HIP(hipDeviceSynchronize());
+    release_workspace(N);
     return FK_OK;
 }
 

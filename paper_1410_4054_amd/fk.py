@@ -130,6 +130,7 @@ def lib():
             "fk_net_destroy": [vp],
             "fk_net_get_weights": [vp, vp, i64],
             "fk_net_set_weights": [vp, vp, i64],
+            "fk_net_set_plane_limit": [vp, i64],
             "fk_net_forward": [vp, vp, i32, i32, vp, vp, vp, vp, vp],
             "fk_net_guess": [vp, vp, i32, i32, vp, vp, vp, i32, vp, P(i32), vp],
             "fk_net_gradient": [vp, vp, i32, i32, vp, vp, vp, vp, vp, P(f64), vp],
@@ -167,7 +168,7 @@ def exported_symbols() -> list[str]:
         "fk_spmv32", "fk_dot",
         "fk_copy",
         "fk_axpby", "fk_net_num_weights", "fk_net_create", "fk_net_destroy", "fk_net_get_weights",
-        "fk_net_set_weights", "fk_net_forward", "fk_net_guess", "fk_net_gradient", "fk_net_train_step",
+        "fk_net_set_weights", "fk_net_set_plane_limit", "fk_net_forward", "fk_net_guess", "fk_net_gradient", "fk_net_train_step",
         "fk_batch_create", "fk_batch_destroy", "fk_batch_shape", "fk_batch_solve", "fk_batch_results",
         "fk_solve_noalloc", "fk_status_str", "fk_last_error", "fk_version",
     ]
@@ -550,6 +551,11 @@ class Net:
         w = np.ascontiguousarray(w, dtype=np.float32)
         _check(lib().fk_net_set_weights(self._h, w.ctypes.data_as(ctypes.c_void_p), w.size),
                "fk_net_set_weights")
+
+    def set_plane_limit(self, nbytes: int):
+        """Bytes of device memory that the gradient planes of the hidden layers
+        may take; above, two are used in turn."""
+        _check(lib().fk_net_set_plane_limit(self._h, int(nbytes)), "fk_net_set_plane_limit")
 
     def forward(self, A: Matrix, nx: int, ny: int, b, um, um1, y, stream=None):
         import torch

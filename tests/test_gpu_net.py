@@ -261,3 +261,27 @@ def test_learned_guess_gain(device):
         assert all(s == fk.OK for s in r.statuses), p
     assert res["learned"].total_iterations < 0.5 * res["prev"].total_iterations
     assert res["learned"].total_iterations < 0.6 * res["extrap"].total_iterations
+
+
+@pytest.mark.parametrize("layers", [2, 3, 4, 5, 8])
+def test_gradient_with_two_planes(layers, device):
+    """Where the hidden layers' gradient planes have no room (here by the
+    caller's limit), two are used in turn: the same gradient bit for bit, before
+    and after the limit is lifted, and the same trained weights."""
+    w = P.net_init(layers, 4)
+    nx, ny = 67, 50
+    M = fk.Matrix(P.heat2d(nx, ny=ny))
+    args = [dev(v) for v in _inputs(nx, ny, 9)]
+    every, two = fk.Net(layers, w), fk.Net(layers, w)
+    print(f"\n[case] net gradient {nx}x{ny}, {layers} layers, two planes", flush=True)
+    ga, la = every.gradient(M, nx, ny, *args)
+    # one byte short of all planes, none at all, exactly all, no limit
+    for limit in ((layers - 1) * 32 * nx * ny - 1, 0, (layers - 1) * 32 * nx * ny, 2**62):
+        two.set_plane_limit(limit)
+        gb, lb = two.gradient(M, nx, ny, *args)
+        assert la == lb and np.array_equal(ga, gb), limit
+    two.set_plane_limit(0)
+    for net in (every, two):
+        for _ in range(3):
+            net.train_step(M, nx, ny, *args, lr=1e-3)
+    assert np.array_equal(every.weights(), two.weights())
