@@ -79,7 +79,7 @@ def update_bytes(n: int) -> int:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("fk_kernels.hip", "fk_internal.hpp", "fk_dd.hpp"):
+    for f in ("fk_kernels.hip", "fk_internal.hpp", "fk_state.hpp", "fk_dd.hpp"):
         with open(os.path.join(ROOT, "paper_1410_4054_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -109,6 +109,17 @@ def time_solves(torch, S, bd, xd, steps):
         its += S.iterations()
     torch.cuda.synchronize()
     return time.perf_counter() - t0, its
+
+
+def launch_per_step_rate(torch, fk, M, method, bd, xd, steps):
+    """Iterations/s of the launch-per-step kernels (a replayed graph of them,
+    which the resident solves do not take)."""
+    S = fk.Solver(M, method=method, rtol=RTOL, record_history=False, graph=True)
+    xd.zero_(); S.solve(bd, xd)
+    t, its = time_solves(torch, S, bd, xd, steps)
+    assert S.resident()[2] == 0
+    S.close()
+    return its / t
 
 
 def copy_bandwidth(torch, fk, nbytes=1 << 30, reps=10):
@@ -316,6 +327,7 @@ def run_case(spec: str, steps: int, warmup: int, layout_arg=None):
     for _ in range(warmup):
         xd.zero_(); S.solve(bd, xd)
     t, its = time_solves(torch, S, bd, xd, steps)
+    resident = S.resident()[2] > 0
     S.close()
     log(f"[case] timed: {its / t:.1f} iterations/s; profile pass")
     S = fk.Solver(M, method=method, record_history=False, profile=True, **kw)
@@ -338,10 +350,10 @@ def run_case(spec: str, steps: int, warmup: int, layout_arg=None):
         for k, byt in cb[tag]["kernels"].items():
             if k in kernel_us:
                 rates[f"{k}_{tag}_GBps"] = byt / (kernel_us[k] * 1e-6) / 1e9
-        if cb[tag]["iteration"]:
+        if cb[tag]["iteration"] and not resident:  # (bytes of the launch-per-step kernels)
             rates[f"iteration_{tag}_GBps"] = cb[tag]["iteration"] * its / t / 1e9
     print(json.dumps({"case": spec, "n": A.n, "nnz": A.nnz, "layout": layout, "entries": entries,
-                      "matrix_bytes": M.matrix_bytes(), "iterations_per_s": its / t,
+                      "matrix_bytes": M.matrix_bytes(), "iterations_per_s": its / t, "resident": resident,
                       "iterations": its, "kernel_us": kernel_us, "bytes": cb, "rates": rates}),
           flush=True)
     M.close()
@@ -481,16 +493,20 @@ def main():
             extras[f"{other}_spmv_dot_GBps"] = spmv_dot_bytes(n, o_bytes) / (o_us * 1e-6) / 1e9
         extras["update_dot_us"] = upd_us
         extras["update_dot_GBps"] = update_bytes(n) / (upd_us * 1e-6) / 1e9
-        # Whole iterations: CSR algorithmic bytes (12 nnz + 76 N + 4) and
-        # those of the layout read, times iterations per second.
+        # Whole iterations of the launch-per-step kernels: CSR algorithmic
+        # bytes (12 nnz + 76 N + 4) and those of the layout read, times their
+        # iterations per second (the timed resident solves keep the vectors on
+        # the chip and move neither).
+        per_step = launch_per_step_rate(torch, fk, M, "cg_pipelined", bd, xd, 5)
+        extras["launch_per_step_iters_per_s"] = per_step
         per_it_bytes = spmv_b + update_bytes(n)
         per_it_layout = spmv_layout_b + update_bytes(n)
         extras["iteration_algorithmic_bytes"] = per_it_bytes
-        extras["iteration_GBps"] = per_it_bytes * value / 1e9
-        extras["iteration_frac_of_peak"] = per_it_bytes * value / 1e9 / PEAK_HBM_GBS
+        extras["iteration_GBps"] = per_it_bytes * per_step / 1e9
+        extras["iteration_frac_of_peak"] = per_it_bytes * per_step / 1e9 / PEAK_HBM_GBS
         extras["iteration_layout_bytes"] = per_it_layout
-        extras["iteration_layout_GBps"] = per_it_layout * value / 1e9
-        extras["iteration_layout_frac_of_peak"] = per_it_layout * value / 1e9 / PEAK_HBM_GBS
+        extras["iteration_layout_GBps"] = per_it_layout * per_step / 1e9
+        extras["iteration_layout_frac_of_peak"] = per_it_layout * per_step / 1e9 / PEAK_HBM_GBS
         extras["copy_kernel_GBps_1GiB"] = copy_bandwidth(torch, fk)
 
         log("[bench] extras: BiCGStab 1024^2, four and two kernels per iteration")
@@ -518,12 +534,14 @@ def main():
             extras[f"{tag}_convdiff2d_1024_iters_per_s"] = its3 / t3
             extras[f"{tag}_convdiff2d_1024_us_per_iter"] = t3 / its3 * 1e6
             extras[f"{tag}_convdiff2d_1024_k"] = S3.iterations()
-            extras[f"{tag}_convdiff2d_1024_iteration_GBps"] = bicg_b * its3 / t3 / 1e9
-            extras[f"{tag}_convdiff2d_1024_iteration_frac_of_peak"] = bicg_b * its3 / t3 / 1e9 / PEAK_HBM_GBS
-            extras[f"{tag}_convdiff2d_1024_iteration_layout_bytes"] = moved[method]
-            extras[f"{tag}_convdiff2d_1024_iteration_layout_frac_of_peak"] = (
-                moved[method] * its3 / t3 / 1e9 / PEAK_HBM_GBS)
             S3.close()
+            # (bytes of the launch-per-step kernels, at their own rate)
+            rate3 = launch_per_step_rate(torch, fk, M3, method, b3d, x3d, 2)
+            extras[f"{tag}_convdiff2d_1024_launch_per_step_iters_per_s"] = rate3
+            extras[f"{tag}_convdiff2d_1024_iteration_GBps"] = bicg_b * rate3 / 1e9
+            extras[f"{tag}_convdiff2d_1024_iteration_frac_of_peak"] = bicg_b * rate3 / 1e9 / PEAK_HBM_GBS
+            extras[f"{tag}_convdiff2d_1024_iteration_layout_bytes"] = moved[method]
+            extras[f"{tag}_convdiff2d_1024_iteration_layout_frac_of_peak"] = moved[method] * rate3 / 1e9 / PEAK_HBM_GBS
             S3 = fk.Solver(M3, method=method, rtol=RTOL, record_history=False, profile=True)
             x3d.zero_(); S3.solve(b3d, x3d)
             kt3 = S3.kernel_times()
@@ -902,8 +920,9 @@ def main():
                      "csr_bytes_per_launch": spmv_b, "csr_achieved": achieved,
                      "csr_frac": achieved / PEAK_HBM_GBS,
                      "note": "kernel times are of a profiled solve, which runs launch per step; the timed "
-                             "solves run resident, in one launch, and move fewer bytes than extra.iteration_* "
-                             "counts. 128^3's working set fits the 256 MB Infinity Cache; "
+                             "solves run resident, in one launch, and move fewer bytes; "
+                             "extra.iteration_* is of the launch-per-step kernels at their own rate, "
+                             "extra.launch_per_step_iters_per_s. 128^3's working set fits the 256 MB Infinity Cache; "
                              "extra.poisson3d_192_* is the point beyond it",
                      "update_dot_avg_us": upd_us},
         "cpu_baseline": cpu,
