@@ -2058,8 +2058,12 @@ static fk_status solve_resident(fk_solver S, const double *b, double *x)
             S->res_epoch = 1;
         }
         a.epoch = S->res_epoch;
-        a.refuse = S->test_decline == S->res_launches + 1;
         S->res_epoch += RES_TAGS;
+        if (S->test_decline == S->res_launches + 1) {  // decided before the workgroups can
+            const uint64_t no = (uint64_t)a.epoch << 2 | 2u;
+            memcpy(&S->h_init[1], &no, sizeof no);
+            HIP_TRY(hipMemcpyAsync(a.decision, &S->h_init[1], sizeof no, hipMemcpyHostToDevice, S->stream));
+        }
         hipError_t e = launch_resident(S->res, a, S->stream);
         if (e != hipSuccess)
             return fail(FK_E_HIP, "resident solve: %s", hipGetErrorString(e));

@@ -381,7 +381,6 @@ struct ResCtl {
 struct ResArgs {
     DevCsr A;
     int32_t rows, gcap, resume, chunk;
-    int32_t refuse;  // 1: workgroup 0 votes against the start (fk_solver_test_resident)
     uint32_t epoch;  // first tag of this launch; it uses at most 2 chunk + 4 of them
     const uint16_t *idx;
     const uint4 *idx4;  // streamed matrices: idx packed, one load per row

@@ -526,7 +526,7 @@ __device__ __forceinline__ bool everyone_here(ResShared &sh, const ResArgs &a, i
                 __builtin_amdgcn_s_sleep(2);
                 cur = load_word(a.decision);
             }
-        const uint64_t say = undecided | (g == 0 && here && !a.refuse ? 1u : 2u);
+        const uint64_t say = undecided | (g == 0 && here ? 1u : 2u);
         while ((cur >> 2) != a.epoch) {
             const uint64_t seen = atomicCAS(reinterpret_cast<unsigned long long *>(a.decision), cur, say);
             cur = seen == cur ? say : seen;
