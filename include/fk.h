@@ -256,8 +256,12 @@ fk_status fk_csr_stream(fk_csr A, int32_t *streaming, int32_t *sweep);
  * is in a sliced layout of at most seven entries per row and whose vectors fit
  * the registers and LDS of the chip (beyond about a million unknowns CG alone,
  * up to two million, reading the matrix from the caches) run as one launch of
- * resident workgroups, with the same iterates (about 50 n bytes more per
- * solver).
+ * resident workgroups, with the same iterates.  Such a solver keeps 33 n bytes
+ * more, 2 per stored entry, 16 n where the matrix is read from the caches, and up
+ * to 40 KB per workgroup (of at most one per compute unit); where memory has no
+ * room for that, it takes the multi-kernel path.
+ * Such a launch holds its compute units until it ends, after 8192 iterations at
+ * the latest; other streams' kernels wait for them.
  * FK_FLAG_GRAPH and FK_FLAG_PROFILE, which replay or time the launches of
  * the multi-kernel path, and the streaming mode keep to that path; so does a
  * solve whose workgroups do not find room on the device beside other work, and

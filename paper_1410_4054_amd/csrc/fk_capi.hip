@@ -113,8 +113,8 @@ public:
         } catch (const std::bad_alloc &) {
             return nullptr;
         }
-        if (hipHostMalloc(reinterpret_cast<void **>(&p.mem), 64 * LINE * sizeof(double), hipHostMallocPortable) !=
-            hipSuccess) {
+        if (hipHostMalloc(reinterpret_cast<void **>(&p.mem), 64 * LINE * sizeof(double),
+                          hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
@@ -1111,10 +1111,15 @@ static bool small_path_ok(fk_csr A, const fk_opts &o)
     const int rpt = small_rows_per_thread(A->n);
     if (rpt == 0 || (bicg && rpt > 2) || A->nnz > 65536 || A->long_rows > 0)
         return false;
-    // Where the grid kernels overtake one workgroup (2D Poisson, 30 fixed
-    // iterations, us per iteration, one workgroup / grid): two-kernel CG
-    // 12.2 / 15.0 at n = 3,969, 16.2 / 16.6 at 6,400, 18.8 / 14.8 at 8,100;
-    // one-kernel CG 9.8 / 11.4 at 2,500, 12.3 / 11.7 at 3,969.
+    // The limits are those of the row-block form (k_small_*), where the grid
+    // kernels overtake one workgroup (2D Poisson, us per iteration, one
+    // workgroup / grid): two-kernel CG 9.9 / 12.6 at n = 3,969, one-kernel CG
+    // 7.6 / 11.0 at 2,500, 8.6 / 11.6 at 3,025, about even at 3,969.  (BiCGStab has
+    // vectors for 2,048 only: 15.3 / 24.3 and 16.9 at 2,025.)  On the sliced
+    // layouts one workgroup runs the resident kernels, and up to 2,048
+    // unknowns nothing is faster (CG 2.3 / 11.9 and 8.5 at 2,025); from there to
+    // these limits several would be (CG 3.4 where one takes 4.1 at 2,116 and
+    // 4.25 at 4,096), which FK_FLAG_NO_SMALL selects.
     if (o.method == FK_CG_PIPELINED && A->n > 4096)
         return false;
     if (o.method == FK_CG_PIPELINED_1K && A->n > 3072)
@@ -1170,15 +1175,16 @@ constexpr uint32_t RES_TAGS = 2 * RES_CHUNK + 8;  // tags a launch may use: two 
 constexpr int32_t RES_REST_MAX = 64;
 // Fewest unknowns of a solve on several resident workgroups; below, one
 // workgroup solves alone (BiCGStab up to 2048 unknowns, the one-kernel CG up
-// to 3072, CG up to 4096), or the caller asked for the multi-kernel path.  us
+// to 3072, CG up to 4096; see small_path_ok), or, with FK_FLAG_NO_SMALL, the
+// multi-kernel path does.  us
 // per iteration, resident / launch per step: 2D Poisson CG 3.4 / 9.7 (one
 // kernel) at n = 3,969, 3.5 / 11.6 at 16,129, 5.3 / 15.6 at 261,121, 9.3 / 29.7
 // at 1,000,000; 3D 5.8 / 17.0 at 262,144, 8.9 / 23.4 at 512,000, 37.3 / 50.8 at
 // 2,097,152 (matrix streamed); BiCGStab on 2D convection-diffusion 7.1 / 19.6
 // at 2,116, 7.1 / 19.3 at 3,969, 11.3 / 26.0 at 261,121, 28.6 / 53 at
 // 1,048,576.  One workgroup, these kernels / the CSR kernels of
-// fk_kernels.hip: CG 2.0 / 3.5 at n = 1,024, 4.4 / 10.1 at 3,969; BiCGStab
-// 4.2 / 8.0 at 1,024.
+// fk_kernels.hip: CG 1.7 / 3.3 at n = 1,024, 4.25 / 9.9 at 3,969; BiCGStab
+// 3.9 / 7.3 at 1,024, 5.2 / 15.4 at 2,025.
 constexpr int64_t RES_MIN_N = 2048;
 
 // Which solves are resident: the pipelined methods on a sliced layout of at
