@@ -881,16 +881,14 @@ hipError_t dalloc(T **p, size_t count)
 // layers on 2000^2: 2.25 ms, 1.84 with all planes; 1100^2: 0.82 and 0.71).
 uint16_t *grad_plane(fk_net N, int l) { return N->g16[l % N->planes]; }
 
-fk_status ensure_workspace(fk_net N, int64_t n)
+hipError_t alloc_workspace(fk_net N, size_t un, int planes)
 {
-    if (N->cap >= n)
-        return FK_OK;
-    release_workspace(N);
-    const size_t un = (size_t)n;
     hipError_t e = hipSuccess;
     e = e ? e : dalloc(&N->feat, un * 4);
     for (int l = 1; l < N->meta.layers && e == hipSuccess; ++l)
         e = dalloc(&N->act[l], un * 16);
+    for (int l = 0; l < planes && e == hipSuccess; ++l)
+        e = dalloc(&N->g16[l], un * 16);
     e = e ? e : dalloc(&N->g4, un * 4);
     e = e ? e : dalloc(&N->y, un);
     e = e ? e : dalloc(&N->target, un);
@@ -902,18 +900,23 @@ fk_status ensure_workspace(fk_net N, int64_t n)
     e = e ? e : dalloc(&N->loss, 1);
     e = e ? e : dalloc(&N->flag, 1);
     e = e ? e : dalloc(&N->xtmp, un);
-    // the gradient planes last: as many as there is room for
-    const int want = N->meta.layers - 1, least = std::min(want, 2);
-    N->planes = want > least && un > N->plane_limit / 32 / (size_t)want ? least : want;
-    for (int l = 0; l < N->planes && e == hipSuccess; ++l) {
-        e = dalloc(&N->g16[l], un * 16);
-        if (e == hipErrorOutOfMemory && l >= least) {
-            (void)hipGetLastError();
-            while (l > least)
-                dfree(N->g16[--l]);
-            N->planes = least;
-            e = hipSuccess;
-        }
+    N->planes = planes;
+    return e;
+}
+
+fk_status ensure_workspace(fk_net N, int64_t n)
+{
+    if (N->cap >= n)
+        return FK_OK;
+    release_workspace(N);
+    const size_t un = (size_t)n;
+    const int all = N->meta.layers - 1, least = std::min(all, 2);
+    const bool room = un <= N->plane_limit / 32 / (size_t)all;
+    hipError_t e = alloc_workspace(N, un, room ? all : least);
+    if (e == hipErrorOutOfMemory && N->planes > least) {
+        (void)hipGetLastError();
+        release_workspace(N);
+        e = alloc_workspace(N, un, least);
     }
     if (e != hipSuccess) {
         release_workspace(N);
