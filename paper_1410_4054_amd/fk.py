@@ -168,7 +168,8 @@ def exported_symbols() -> list[str]:
         "fk_spmv32", "fk_dot",
         "fk_copy",
         "fk_axpby", "fk_net_num_weights", "fk_net_create", "fk_net_destroy", "fk_net_get_weights",
-        "fk_net_set_weights", "fk_net_set_plane_limit", "fk_net_forward", "fk_net_guess", "fk_net_gradient", "fk_net_train_step",
+        "fk_net_set_weights", "fk_net_set_plane_limit", "fk_net_forward", "fk_net_guess", "fk_net_gradient",
+        "fk_net_train_step",
         "fk_batch_create", "fk_batch_destroy", "fk_batch_shape", "fk_batch_solve", "fk_batch_results",
         "fk_solve_noalloc", "fk_status_str", "fk_last_error", "fk_version",
     ]
